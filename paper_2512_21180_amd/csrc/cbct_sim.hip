@@ -47,10 +47,29 @@ __device__ inline double unif53(uint32_t a, uint32_t b)
     return ((double)(a >> 5) * 67108864.0 + (double)(b >> 6)) * (1.0 / 9007199254740992.0);
 }
 
+// ln k! of a whole k >= 0: Stirling's series from 16 up (its first left-out
+// term is below 1e-16 there), the logarithm of the exact product below.
+__device__ inline double ln_factorial(double k)
+{
+    if (k < 16.0) {
+        double f = 1.0;
+        for (double j = 2.0; j <= k; j += 1.0)
+            f *= j;
+        return log(f);
+    }
+    const double r = 1.0 / k, r2 = r * r;
+    double s = fma(r2, -691.0 / 360360.0, 1.0 / 1188.0);
+    s = fma(r2, s, -1.0 / 1680.0);
+    s = fma(r2, s, 1.0 / 1260.0);
+    s = fma(r2, s, -1.0 / 360.0);
+    s = fma(r2, s, 1.0 / 12.0);
+    return fma(k + 0.5, log(k), -k) + (0.9189385332046727 + r * s);
+}
+
 // Poisson(lam): CDF inversion below 10, Hormann's PTRS from 10 up.  Trial j
 // of the variate uses counter word 2 = trial0 + j.
-__device__ int64_t poisson(double lam, uint64_t seed, uint32_t sid, uint64_t i,
-                           uint32_t trial0 = 0)
+__device__ __forceinline__ int64_t poisson(double lam, uint64_t seed, uint32_t sid, uint64_t i,
+                                           uint32_t trial0)
 {
     if (!(lam > 0.0))
         return 0;
@@ -81,7 +100,7 @@ __device__ int64_t poisson(double lam, uint64_t seed, uint32_t sid, uint64_t i,
             return (int64_t)kf;
         if (kf < 0.0 || (us < 0.013 && V > us))
             continue;
-        if (log(V) + log_inv_alpha - log(a / (us * us) + b) <= -lam + kf * ll - lgamma(kf + 1.0))
+        if (log(V) + log_inv_alpha - log(a / (us * us) + b) <= -lam + kf * ll - ln_factorial(kf))
             return (int64_t)kf;
     }
     return (int64_t)floor(lam + 0.5);
@@ -98,13 +117,280 @@ __global__ void __launch_bounds__(kT) k_philox(size_t n, uint64_t seed, uint32_t
     reinterpret_cast<uint4 *>(out)[i] = v;
 }
 
-__global__ void __launch_bounds__(kT) k_poisson_log(size_t n, const float *p, float *y, int64_t *cnt,
+// ---- Poisson counts of a wave's elements --------------------------------------
+//
+// `poisson` alone, one thread per element, is bound by FP64 issue: a wave
+// follows its slowest lane through logarithms, lgamma and further trials,
+// about 3000 vector instructions per variate.  `WavePoisson` decides the same
+// tests from cheaper values with bounds on their errors:
+//   * lam from a 64-entry table and a degree-5 polynomial (relative error
+//     below 1e-15, taken as 1e-12 and more wherever it enters);
+//   * from a mean of 10 up the first trial's immediate acceptance in FP32
+//     (four in five variates); below 10 the inversion with tabulated 1 / k;
+//   * what is left goes to a queue of the wave in LDS and is tested 64 at a
+//     time, every lane with an item of its own: the count in FP64, the
+//     acceptance test as k (log1p(x) - x) with x = (lam - k) / k in FP32,
+//     Stirling's series for the rest; a rejected item returns to the queue
+//     with its next trial.
+// A decision closer to its threshold than the error bound is taken by
+// `poisson` itself, so the counts are `poisson`'s own.  Clinical scan, ten
+// bins (9.4e8 variates): see k_sim_poly.
+constexpr int kQueue = 128;        // at most 63 left by a drain plus 64 pushed
+constexpr uint32_t kExact = 255;   // trial field of an item `poisson` decides
+constexpr double kLamMax = 1e7;    // above it `poisson` decides
+
+struct PoissonLds {
+    double exp2_64[64];            // 2^(j / 64)
+    double inv[64];                // 1 / k
+};
+
+__device__ inline void poisson_tables(PoissonLds &T)
+{
+    if (threadIdx.x < 64) {
+        T.exp2_64[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 64.0));
+        T.inv[threadIdx.x] = 1.0 / (double)threadIdx.x;
+    }
+    __syncthreads();
+}
+
+// exp(x) for |x| <= 700: 2^(n/64) times the polynomial of |r| <= ln2 / 128
+__device__ inline double exp_table(const PoissonLds &T, double x)
+{
+    const double nf = rint(x * 92.33248261689366);            // 64 / ln 2
+    // ln 2 / 64 in two parts, the first of 25 bits
+    double r = fma(nf, -0x1.62e42fp-7, x);
+    r = fma(nf, -0x1.df473de6af279p-32, r);
+    const int n = (int)nf;
+    double q = fma(r, 1.0 / 120.0, 1.0 / 24.0);
+    q = fma(r, q, 1.0 / 6.0);
+    q = fma(r, q, 0.5);
+    q = fma(r, q, 1.0);
+    const double t = T.exp2_64[n & 63];
+    return ldexp(fma(t * r, q, t), n >> 6);
+}
+
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One wave's counts: lane l holds element base + l, `lam_of(lane, bin)` gives
+// an element's exact mean, count[bin * 64 + lane] receives the counts.
+template <class LamOf>
+struct WavePoisson {
+    const PoissonLds &T;
+    double *qlam;                  // [kQueue]
+    uint32_t *qid;                 // [kQueue] lane | bin << 8 | trial << 16
+    int64_t *count;
+    uint64_t seed;
+    uint32_t sid;
+    uint64_t base;
+    const LamOf &lam_of;
+    int queued = 0;                // wave uniform
+
+    __device__ void push(bool p, double lam, uint32_t id)
+    {
+        const uint64_t m = __ballot(p);
+        const int at = queued + (int)__builtin_amdgcn_mbcnt_hi(
+                                    (uint32_t)(m >> 32),
+                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (p) {
+            qlam[at] = lam;
+            qid[at] = id;
+        }
+        queued += (int)__popcll(m);
+        wave_lds_fence();
+    }
+
+    // bin e of the lane's element: mean i0 exp(-att)
+    __device__ void first(int e, bool live, int lane, double i0, double att)
+    {
+        int64_t c = 0;
+        bool todo = false;
+        uint32_t trial = 0;
+        double lam = 0.0;
+        // exp(-att) underflows to zero from 746 on
+        if (live && i0 > 0.0 && !(att > 760.0 && i0 < 1e38)) {
+            if (!(fabs(att) <= 700.0 && i0 < 1e30)) {
+                todo = true;
+                trial = kExact;
+            } else {
+                lam = i0 * exp_table(T, -att);
+                const Words d = draw(seed, sid, base + lane, 256u * (uint32_t)e);
+                if (lam < 10.0 - 1e-9) {
+                    const double u = unif53(d.w[0], d.w[1]);
+                    double p = exp_table(T, -lam), F = p;
+                    // F's error is below 1e-14: sixty terms of three roundings
+                    bool near = fabs(u - F) < 1e-13, on = u > F;
+                    int k = 0;
+#pragma unroll 1
+                    for (int t = 1; t < 64 && on; ++t) {
+                        p *= lam * T.inv[t];
+                        F += p;
+                        k = t;
+                        on = u > F;
+                        near |= fabs(u - F) < 1e-13;
+                    }
+                    c = k;
+                    todo = near || on;
+                    trial = kExact;
+                } else if (!(lam > 10.0 + 1e-9 && lam < kLamMax)) {
+                    todo = true;
+                    trial = kExact;
+                } else {
+                    // FP32 values of the first trial: |U|, us and V err by at
+                    // most 2^-23 of themselves plus 2^-32, the slope by a few
+                    // 2^-23 of itself
+                    const float sl = __builtin_amdgcn_sqrtf((float)lam);
+                    const float b = fmaf(2.53f, sl, 0.931f);
+                    const float a = fmaf(0.02483f, b, -0.059f);
+                    const float vr = fmaf(-3.6224f, __builtin_amdgcn_rcpf(b - 2.0f), 0.9277f);
+                    const float U = (float)(int)(d.w[0] ^ 0x80000000u) * 0x1p-32f;
+                    const float V = (float)d.w[2] * 0x1p-32f;
+                    const float us = 0.5f - fabsf(U);
+                    const float slope = fmaf(2.0f * a, __builtin_amdgcn_rcpf(us), b);
+                    const double t = (lam + 0.43) + (double)(slope * U);
+                    const double kf = floor(t);
+                    const float fr = (float)(t - kf), mar = 1e-6f * slope;
+                    c = (int64_t)(int)kf;
+                    todo = !(us >= 0.070001f && V <= vr - 4e-6f && fr > mar && fr < 1.0f - mar);
+                }
+            }
+        }
+        if (live)
+            count[e * 64 + lane] = c;
+        push(todo, lam, (uint32_t)lane | (uint32_t)e << 8 | trial << 16);
+    }
+
+    // the last min(64, queued) items: one trial each
+    __device__ void drain(int lane)
+    {
+        const int nb = queued < 64 ? queued : 64;
+        queued -= nb;
+        const bool on = lane < nb;
+        const int at = queued + (on ? lane : 0);
+        const double lam = qlam[at];
+        const uint32_t id = qid[at];
+        wave_lds_fence();
+        const uint32_t el = id & 63u, e = (id >> 8) & 255u, j = id >> 16;
+        bool exact = on && j >= 64u, again = false;
+        int64_t c = 0;
+        if (on && !exact) {
+            const Words d = draw(seed, sid, base + el, 256u * e + j);
+            const double U = unif53(d.w[0], d.w[1]) - 0.5, V = unif53(d.w[2], d.w[3]);
+            const double us = 0.5 - fabs(U);
+            const double b = 0.931 + 2.53 * sqrt(lam);
+            const double a = -0.059 + 0.02483 * b;
+            const double vr = 0.9277 - 3.6224 / (b - 2.0);
+            const double arg = (2.0 * a / us + b) * U + lam + 0.43;
+            const double kf = floor(arg), m = 1e-12 * (fabs(arg) + lam);
+            exact = !(arg - kf > m && arg - kf < 1.0 - m) || fabs(V - vr) < 1e-11;
+            c = (int64_t)kf;
+            if (!(us >= 0.07 && V <= vr)) {
+                if (kf < 0.0 || (us < 0.013 && V > us)) {
+                    again = true;
+                } else if (kf < 2.0 || kf > 2.0 * kLamMax) {
+                    exact = true;
+                } else {
+                    const float bf = (float)b, af = (float)a, uf = (float)us, kk = (float)kf;
+                    // log(V / alpha / (a / us^2 + b))
+                    const float ia = fmaf(1.1328f, __builtin_amdgcn_rcpf(bf - 3.4f), 1.1239f);
+                    const float lhs = __logf((float)V * ia) -
+                                      __logf(fmaf(af, __builtin_amdgcn_rcpf(uf * uf), bf));
+                    // -lam + k log(lam) - log(k!) by Stirling's series
+                    const float ik = 1.0f / kk, x = (float)(lam - kf) * ik;
+                    const float t = x / (2.0f + x), t2 = t * t;
+                    float g;
+                    if (fabsf(t) < 0.2f) {
+                        // log1p(x) - x = 2 atanh(t) - x = 2 t^3 (1/3 + t^2/5 + ..) - x t
+                        g = fmaf(t2, fmaf(t2, fmaf(t2, 1.0f / 11.0f, 1.0f / 9.0f), 1.0f / 7.0f),
+                                 0.2f);
+                        g = fmaf(2.0f * t * t2, fmaf(t2, g, 1.0f / 3.0f), -x * t);
+                    } else {
+                        g = __logf(1.0f + x) - x;
+                    }
+                    const float i2 = ik * ik;
+                    const float st = ik * fmaf(i2, fmaf(i2, 1.0f / 1260.0f, -1.0f / 360.0f),
+                                               1.0f / 12.0f);
+                    const float rhs = fmaf(kk, g, -0.5f * __logf(6.28318531f * kk)) - st;
+                    const float diff = lhs - rhs;
+                    // errors: lhs 2e-6 of its size (up to 60) plus 1e-6, rhs a
+                    // few 1e-7 of its size, and 5e-6 from the series at k = 2
+                    const float mar = 2e-4f + 4e-6f * fabsf(rhs);
+                    exact = exact || !(fabsf(diff) > mar);
+                    again = diff > 0.0f;
+                }
+            }
+            again = again && !exact;
+        }
+        if (exact) {
+            c = poisson(lam_of((int)el, (int)e), seed, sid, base + el, 256u * e);
+        }
+        if (on && !again)
+            count[e * 64 + el] = c;
+        push(again, lam, id + 0x10000u);
+    }
+
+    // every bin's first trials, the queue drained whenever it holds a wave
+    template <class Bin>
+    __device__ void run(int bins, bool live, int lane, Bin &&beam)
+    {
+#pragma unroll 1
+        for (int e = 0; e <= bins; ++e) {
+            if (e < bins) {
+                double i0 = 0.0, att = 0.0;
+                if (live)
+                    beam(e, i0, att);
+                first(e, live, lane, i0, att);
+            }
+#pragma unroll 1
+            while (queued >= (e < bins ? 64 : 1))
+                drain(lane);
+        }
+        wave_lds_fence();
+    }
+};
+
+// Threads of a workgroup and its dynamic LDS: above 16 bins two waves, which
+// keeps the counts of 32 bins under 64 KB.
+int poisson_threads(int bins) { return bins > 16 ? 128 : kT; }
+
+size_t poisson_lds_bytes(int bins)
+{
+    return (size_t)(poisson_threads(bins) / 64) * (kQueue * 12 + (size_t)bins * 64 * 8);
+}
+
+template <class LamOf>
+__device__ inline WavePoisson<LamOf> wave_poisson(const PoissonLds &T, char *lds, int wave,
+                                                  int bins, uint64_t seed, uint32_t sid,
+                                                  uint64_t base, const LamOf &f)
+{
+    char *w = lds + (size_t)wave * (kQueue * 12 + (size_t)bins * 64 * 8);
+    double *ql = reinterpret_cast<double *>(w);
+    int64_t *cnt = reinterpret_cast<int64_t *>(w + kQueue * 8);
+    uint32_t *qi = reinterpret_cast<uint32_t *>(w + kQueue * 8 + (size_t)bins * 64 * 8);
+    return WavePoisson<LamOf>{T, ql, qi, cnt, seed, sid, base, f};
+}
+
+__global__ void __launch_bounds__(kT, 4) k_poisson_log(size_t n, const float *p, float *y, int64_t *cnt,
                                                     double I0, uint64_t seed, uint32_t sid)
 {
-    const size_t i = (size_t)blockIdx.x * kT + threadIdx.x;
-    if (i >= n)
+    extern __shared__ __align__(16) char lds[];
+    __shared__ PoissonLds T;
+    poisson_tables(T);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const size_t base = (size_t)blockIdx.x * blockDim.x + 64 * wave, i = base + lane;
+    const bool live = i < n;
+    auto lam_of = [&](int l, int) { return I0 * exp(-(double)p[base + l]); };
+    auto W = wave_poisson(T, lds, wave, 1, seed, sid, base, lam_of);
+    W.run(1, live, lane, [&](int, double &i0, double &att) {
+        i0 = I0;
+        att = (double)p[i];
+    });
+    if (!live)
         return;
-    const int64_t c = poisson(I0 * exp(-(double)p[i]), seed, sid, i);
+    const int64_t c = W.count[lane];
     if (cnt)
         cnt[i] = c;
     const double r = (double)(c < 1 ? 1 : c) / I0;
@@ -150,28 +436,42 @@ struct PolyArgs {
 // negative log over the noise-free air signal, clamped at one.  The means and
 // sums are FP64 in bin order (the Poisson acceptance test runs in FP64), so
 // the counts equal those of an FP64 evaluation of the same model.
-__global__ void __launch_bounds__(kT) k_sim_poly(PolyArgs A, const float *pw, const float *pb,
+__global__ void __launch_bounds__(kT, 4) k_sim_poly(PolyArgs A, const float *pw, const float *pb,
                                                  const float *I0, uint64_t seed, uint32_t sid,
                                                  float *y, float *signal, int64_t *counts)
 {
-    const size_t i = (size_t)blockIdx.x * kT + threadIdx.x;
-    if (i >= A.n)
+    extern __shared__ __align__(16) char lds[];
+    __shared__ PoissonLds T;
+    poisson_tables(T);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const size_t base = (size_t)blockIdx.x * blockDim.x + 64 * wave, i = base + lane;
+    const bool live = i < A.n;
+    const size_t pix = live ? i % A.npix : 0;
+    const double w = live ? (double)pw[i] : 0.0, b = live ? (double)pb[i] : 0.0;
+    // the two products rounded, then summed
+    auto att_of = [&](int e, double w, double b) {
+#pragma clang fp contract(off)
+        return A.mu_w[e] * w + A.mu_b[e] * b;
+    };
+    auto lam_of = [&](int l, int e) {
+        const size_t k = base + l;
+        return (double)I0[(size_t)e * A.npix + k % A.npix] *
+               exp(-att_of(e, (double)pw[k], (double)pb[k]));
+    };
+    auto W = wave_poisson(T, lds, wave, A.nbins, seed, sid, base, lam_of);
+    W.run(A.nbins, live, lane, [&](int e, double &i0, double &att) {
+        i0 = (double)I0[(size_t)e * A.npix + pix];
+        att = att_of(e, w, b);
+    });
+    if (!live)
         return;
-    const size_t pix = i % A.npix;
-    const double w = (double)pw[i], b = (double)pb[i];
     double sig = 0.0, air = 0.0;
     for (int e = 0; e < A.nbins; ++e) {
-        const double i0 = (double)I0[(size_t)e * A.npix + pix];
-        double att;
-        {
-#pragma clang fp contract(off)
-            att = A.mu_w[e] * w + A.mu_b[e] * b;   // the two products rounded, then summed
-        }
-        const int64_t c = poisson(i0 * exp(-att), seed, sid, i, 256u * (uint32_t)e);
+        const int64_t c = W.count[e * 64 + lane];
         if (counts)
             counts[(size_t)e * A.n + i] = c;
         sig += A.resp[e] * (double)c;
-        air += A.resp[e] * i0;
+        air += A.resp[e] * (double)I0[(size_t)e * A.npix + pix];
     }
     if (signal)
         signal[i] = (float)sig;
@@ -237,7 +537,7 @@ extern "C" cbct_status cbct_sim_poisson_log(size_t n, const float *p, float *y, 
         return CBCT_OK;
     if (n / kT >= 0x7fffffffu)
         return CBCT_E_SHAPE;
-    hipLaunchKernelGGL(k_poisson_log, grid_for(n), dim3(kT), 0, (hipStream_t)stream, n, p, y,
+    hipLaunchKernelGGL(k_poisson_log, grid_for(n), dim3(kT), poisson_lds_bytes(1), (hipStream_t)stream, n, p, y,
                        counts, I0, seed, stream_id);
     return sim_done(hipGetLastError());
 }
@@ -311,7 +611,9 @@ extern "C" cbct_status cbct_sim_poly(size_t n, size_t npix, const float *pw, con
         if (resp[e] > 0.0 && (A.r_min == 0.0 || resp[e] < A.r_min))
             A.r_min = resp[e];
     }
-    hipLaunchKernelGGL(k_sim_poly, grid_for(n), dim3(kT), 0, (hipStream_t)stream, A, pw, pb, I0,
+    const unsigned bt = (unsigned)poisson_threads(n_bins);
+    hipLaunchKernelGGL(k_sim_poly, dim3((unsigned)((n + bt - 1) / bt)), dim3(bt),
+                       poisson_lds_bytes(n_bins), (hipStream_t)stream, A, pw, pb, I0,
                        seed, stream_id, y, signal, counts);
     return sim_done(hipGetLastError());
 }
