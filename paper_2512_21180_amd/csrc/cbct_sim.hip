@@ -24,8 +24,10 @@ __device__ inline Words philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c
 {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
+        // one v_mad_u64_u32 each
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+        const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
         const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
         c0 = n0;
         c1 = lo1;
@@ -220,20 +222,25 @@ struct WavePoisson {
                 const Words d = draw(seed, sid, base + lane, 256u * (uint32_t)e);
                 if (lam < 10.0 - 1e-9) {
                     const double u = unif53(d.w[0], d.w[1]);
-                    double p = exp_table(T, -lam), F = p;
-                    // F's error is below 1e-14: sixty terms of three roundings
-                    bool near = fabs(u - F) < 1e-13, on = u > F;
-                    int k = 0;
+                    // left = u - F after each term: the count is the number of
+                    // terms it stays above zero (four terms a turn, no branch
+                    // in them: one a turn spent its time in the loop's masks).
+                    // Its error is below 1e-14: sixty terms of three roundings.
+                    double p = exp_table(T, -lam), left = u - p;
+                    double least = fabs(left);
+                    int k = left > 0.0;
 #pragma unroll 1
-                    for (int t = 1; t < 64 && on; ++t) {
-                        p *= lam * T.inv[t];
-                        F += p;
-                        k = t;
-                        on = u > F;
-                        near |= fabs(u - F) < 1e-13;
+                    for (int t = 1; t < 61 && __any(left > 0.0); t += 4) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            p *= lam * T.inv[t + q];
+                            left -= p;
+                            least = fmin(least, fabs(left));
+                            k += left > 0.0;
+                        }
                     }
                     c = k;
-                    todo = near || on;
+                    todo = least < 1e-13 || left > 0.0;
                     trial = kExact;
                 } else if (!(lam > 10.0 + 1e-9 && lam < kLamMax)) {
                     todo = true;
