@@ -10,17 +10,20 @@
 // once for the optical depth to the volume's exit, which gives the escape
 // probability p0 and the weight factor 1 - p0, and once to the depth
 // -log(1 - (1 - p0) u), which gives the interaction point.
-// Integration: a workgroup holds 64 pixels and 16 record phases, one phase
+// Integration: a workgroup holds 8 x 8 pixels and 8 record phases, one phase
 // per wave (every lane of a wave reads the same record, so its loads are
 // uniform); per record a march from the interaction point to the pixel
 // centre gives the two material line integrals, from which the escape
 // probabilities at the incoming and the Compton energy follow by linearity.
-// Each pixel's 16 phase sums are added in phase order: deterministic.
+// Each pixel's 8 phase sums are added in phase order, and where the records
+// are cut into chunks (one workgroup per tile and chunk) the chunks' sums in
+// chunk order: deterministic.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 
 #include "cbct_internal.h"
+#include "cbct_lds.h"
 #include "cbct_scatter.h"
 
 namespace cbct {
@@ -165,6 +168,91 @@ __device__ inline float walk(const Grid &G, const float p[3], const float d[3], 
     return t1;
 }
 
+// Both materials' line integrals along p + t d (|d| = 1) from t = 0 to tmax:
+// `walk`'s segments, summed by a loop made for it.  Every step is the three
+// crossing parameters' minimum, one segment length, one load of the voxel's
+// two densities and three conditional advances of a linear voxel offset, some
+// 20 vector instructions (walk's indexed arrays and 64-bit voxel numbers take
+// several times that); four steps' loads leave together before their sums.
+// Steps past the end have zero length.  A crossing of the exit face that
+// rounds to the end of the walk or below it steps out of the volume by one
+// voxel: the packed densities (one float2 per voxel, read through a buffer
+// resource) have a border of zeros for that; from the two separate volumes a
+// finished walk reads nothing.
+template <bool PACKED>
+__device__ inline float2 line_integrals(const Grid &G, const __amdgpu_buffer_rsrc_t &two,
+                                        const float p[3], const float d[3], float tmax)
+{
+    const int n[3] = {G.nx, G.ny, G.nz};
+    const float v[3] = {G.vx, G.vy, G.vz}, lo[3] = {G.lox, G.loy, G.loz};
+    float inv[3], t0 = 0.0f, t1 = tmax;
+    bool miss = false;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const float hi = lo[q] + (float)n[q] * v[q];
+        inv[q] = 1.0f / d[q];
+        if (d[q] == 0.0f) {
+            miss = miss || !(p[q] > lo[q] && p[q] < hi);
+        } else {
+            const float ta = (lo[q] - p[q]) * inv[q], tb = (hi - p[q]) * inv[q];
+            t0 = fmaxf(t0, fminf(ta, tb));
+            t1 = fminf(t1, fmaxf(ta, tb));
+        }
+    }
+    float2 s = make_float2(0.0f, 0.0f);
+    if (miss || !(t1 > t0))
+        return s;
+    const float te = t1 - t0;
+    const float tm = fminf(1e-4f * fminf(v[0], fminf(v[1], v[2])), 0.5f * te);
+    constexpr uint32_t kUnit = PACKED ? 8u : 1u, kPad = PACKED ? 2u : 0u;
+    const uint32_t stride[3] = {kUnit, kUnit * ((uint32_t)n[0] + kPad),
+                                kUnit * ((uint32_t)n[0] + kPad) * ((uint32_t)n[1] + kPad)};
+    float tn[3], dt[3];
+    uint32_t inc[3], off = PACKED ? stride[0] + stride[1] + stride[2] : 0u;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const float pe = fmaf(t0, d[q], p[q]), x = fmaf(tm, d[q], pe);
+        const int i = min(max((int)floorf((x - lo[q]) / v[q]), 0), n[q] - 1);
+        off += (uint32_t)i * stride[q];
+        const bool up = d[q] > 0.0f, on = d[q] != 0.0f;
+        inc[q] = up ? stride[q] : 0u - stride[q];
+        dt[q] = on ? v[q] * fabsf(inv[q]) : 0.0f;
+        tn[q] = on ? (lo[q] + (float)(i + up) * v[q] - pe) * inv[q] : INFINITY;
+    }
+    const uint32_t nvox = (uint32_t)n[0] * (uint32_t)n[1] * (uint32_t)n[2];
+    const int steps = n[0] + n[1] + n[2] + 4;
+    float t = 0.0f;   // from the entry point
+#pragma unroll 1
+    for (int k = 0; k < steps && t < te; k += 4) {
+        float len[4];
+        float2 r[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float to = fminf(fminf(tn[0], fminf(tn[1], tn[2])), te);
+            len[j] = to - t;
+            t = to;
+            if constexpr (PACKED) {
+                const auto b = __builtin_amdgcn_raw_buffer_load_b64(two, (int)off, 0, 0);
+                r[j] = make_float2(__uint_as_float(b[0]), __uint_as_float(b[1]));
+            } else {
+                const bool in = len[j] != 0.0f && off < nvox;
+                r[j] = in ? make_float2(G.rw[off], G.rb[off]) : make_float2(0.0f, 0.0f);
+            }
+            const bool c0 = tn[0] <= to, c1 = tn[1] <= to, c2 = tn[2] <= to;
+            off += (c0 ? inc[0] : 0u) + (c1 ? inc[1] : 0u) + (c2 ? inc[2] : 0u);
+            tn[0] += c0 ? dt[0] : 0.0f;
+            tn[1] += c1 ? dt[1] : 0.0f;
+            tn[2] += c2 ? dt[2] : 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            s.x = fmaf(len[j], r[j].x, s.x);
+            s.y = fmaf(len[j], r[j].y, s.y);
+        }
+    }
+    return s;
+}
+
 __device__ inline void normalise(float v[3])
 {
     const float r = rsqrtf(fmaf(v[0], v[0], fmaf(v[1], v[1], v[2] * v[2])));
@@ -290,29 +378,41 @@ struct IntArgs {
     float nx_, ny_;          // panel normal (z = 0)
     long nrec;
     const float *rec;        // [nrec][8]
-    float *out;              // [nv][nu]
+    const float2 *two;       // both densities per voxel, or null
+    int tiles_u, chunks;     // pixel tiles along u, chunks of the records
+    float *out;              // [chunks][nv][nu]
 };
 
-// One workgroup: 64 pixels x 16 record phases, one phase per wave (wave p
-// takes records p, p + 16, ...; all its lanes read the same record); the
-// sixteen partial sums of a pixel are added in phase order.
-constexpr int kPixTile = 64, kPhases = 16;
+// One workgroup: 8 x 8 pixels x 8 record phases, one phase per wave (wave p
+// takes records p, p + 8, ...; all its lanes read the same record); the
+// eight partial sums of a pixel are added in phase order.  Square tiles
+// keep a wave's rays in one narrow bundle, whose voxels share cache lines
+// and whose marches end together.  Bound by VALU issue (78 % of the slots;
+// some 20 instructions a step, 400 more a march).  3072 records toward 128^2
+// pixels from 256^3 voxels: 35.9 ms with 64 x 1 pixels, walk and one load per
+// density, 7.0 ms so with 16 phases at 64 registers (spills), 6.84 at 81, 6.60 ms with
+// 8 phases at 80 (six waves per SIMD in three workgroups of a CU instead of
+// four in one).
+constexpr int kPixEdge = 8, kPixTile = kPixEdge * kPixEdge, kPhases = 8;
 
-__global__ void __launch_bounds__(kPixTile * kPhases) k_scatter_integrate(IntArgs A)
+template <bool PACKED>
+__global__ void __launch_bounds__(kPixTile * kPhases, 6) k_scatter_integrate(IntArgs A)
 {
     __shared__ float part[kPhases][kPixTile];
     const int lane = threadIdx.x % kPixTile;
     const int ph = __builtin_amdgcn_readfirstlane(threadIdx.x / kPixTile);
-    const int pix = blockIdx.x * kPixTile + lane;
-    const bool live = pix < A.nu * A.nv;
+    const int iu = (blockIdx.x % A.tiles_u) * kPixEdge + lane % kPixEdge;
+    const int iv = (blockIdx.x / A.tiles_u) * kPixEdge + lane / kPixEdge;
+    const bool live = iu < A.nu && iv < A.nv;
     const Grid &G = A.G;
     const Xs &X = A.X;
-    const int pc = live ? pix : 0;
-    const int iu = pc % A.nu, iv = pc / A.nu;
+    const __amdgpu_buffer_rsrc_t two = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)A.two, (short)0, (int)(8u * ((uint32_t)G.nx + 2u) * ((uint32_t)G.ny + 2u) * ((uint32_t)G.nz + 2u)),
+        kBufferWord3);
     const float pu = ((float)iu - A.cu) * A.du, pv = ((float)iv - A.cv) * A.dv;
     const float P[3] = {fmaf(pu, A.eux, A.Dx), fmaf(pu, A.euy, A.Dy), A.Dz + pv};
     float acc = 0.0f;
-    for (long r = ph; r < A.nrec; r += kPhases) {
+    for (long r = ph + kPhases * blockIdx.y; r < A.nrec; r += kPhases * A.chunks) {
         const float *q = A.rec + 8 * r;
         const float w = q[7];
         if (!(w > 0.0f) || !live)
@@ -328,15 +428,11 @@ __global__ void __launch_bounds__(kPixTile * kPhases) k_scatter_integrate(IntArg
         vs[2] *= id;
         const float cth = fmaf(q[3], vs[0], fmaf(q[4], vs[1], q[5] * vs[2]));
         const float ec = e / (1.0f + e * (1.0f - cth) / kMeC2);
-        float Pw = 0.0f, Pb = 0.0f;
-        walk(G, x, vs, dist, [&](float len, long vi, float) {
-            Pw = fmaf(len, G.rw[vi], Pw);
-            Pb = fmaf(len, G.rb[vi], Pb);
-            return true;
-        });
+        const float2 path = line_integrals<PACKED>(G, two, x, vs, dist);
         int k, kc;
         float f, fc;
         e_pos(X, e, k, f);
+        k = __builtin_amdgcn_readfirstlane(k);   // one energy per record
         e_pos(X, ec, kc, fc);
         const float mw = mu_tot(X, 0, k, f), mb = mu_tot(X, 1, k, f);
         const long vi = voxel_at(G, x[0], x[1], x[2]);
@@ -352,8 +448,9 @@ __global__ void __launch_bounds__(kPixTile * kPhases) k_scatter_integrate(IntArg
             sr = fmaf(fm[m] * mu_kind(X, m, 2, k, f) / mt,
                       table2(X.dens + (m * 2 + 1) * X.K * X.I, X.I, k, f, sd), sr);
         }
-        const float p0c = expf(-fmaf(mu_tot(X, 0, kc, fc), Pw, mu_tot(X, 1, kc, fc) * Pb));
-        const float p0r = expf(-fmaf(mw, Pw, mb * Pb));
+        const float p0c =
+            expf(-fmaf(mu_tot(X, 0, kc, fc), path.x, mu_tot(X, 1, kc, fc) * path.y));
+        const float p0r = expf(-fmaf(mw, path.x, mb * path.y));
         const float s = fmaf(sc * p0c, resp(ec), sr * p0r * resp(e));
         const float cn = fabsf(fmaf(A.nx_, vs[0], A.ny_ * vs[1]));
         acc = fmaf(s * w * cn, A.du * A.dv / r2, acc);
@@ -364,8 +461,36 @@ __global__ void __launch_bounds__(kPixTile * kPhases) k_scatter_integrate(IntArg
         float v = part[0][lane];
         for (int k = 1; k < kPhases; ++k)
             v += part[k][lane];
-        A.out[pix] = v;
+        A.out[((size_t)blockIdx.y * A.nv + iv) * A.nu + iu] = v;
     }
+}
+
+// The packed densities: [nz + 2][ny + 2][nx + 2] pairs, zero on the border.
+__global__ void __launch_bounds__(kT) k_pack_two(Grid G, float2 *two)
+{
+    const uint32_t px = (uint32_t)G.nx + 2u, py = (uint32_t)G.ny + 2u, pz = (uint32_t)G.nz + 2u;
+    const uint32_t i = blockIdx.x * (uint32_t)kT + threadIdx.x;
+    if (i >= px * py * pz)
+        return;
+    const uint32_t x = i % px - 1u, y = i / px % py - 1u, z = i / (px * py) - 1u;
+    float2 v = make_float2(0.0f, 0.0f);
+    if (x < (uint32_t)G.nx && y < (uint32_t)G.ny && z < (uint32_t)G.nz) {
+        const size_t k = ((size_t)z * G.ny + y) * G.nx + x;
+        v = make_float2(G.rw[k], G.rb[k]);
+    }
+    two[i] = v;
+}
+
+__global__ void __launch_bounds__(kT) k_sum_chunks(int n, int chunks, const float *part,
+                                                   float *out)
+{
+    const int i = blockIdx.x * kT + threadIdx.x;
+    if (i >= n)
+        return;
+    float v = part[i];
+    for (int c = 1; c < chunks; ++c)
+        v += part[(size_t)c * n + i];
+    out[i] = v;
 }
 
 cbct_status scat_done(hipError_t e)
@@ -478,7 +603,58 @@ extern "C" cbct_status cbct_scatter_integrate(const cbct_geom *g, const float *r
     A.rec = rec;
     A.out = out;
     const int npix = d.nu * d.nv;
-    hipLaunchKernelGGL(k_scatter_integrate, dim3((unsigned)((npix + kPixTile - 1) / kPixTile)),
-                       dim3(kPixTile * kPhases), 0, (hipStream_t)stream, A);
+    A.tiles_u = (d.nu + kPixEdge - 1) / kPixEdge;
+    const unsigned tiles =
+        (unsigned)A.tiles_u * (unsigned)((d.nv + kPixEdge - 1) / kPixEdge);
+    A.chunks = 1;
+    A.two = nullptr;
+    hipStream_t st = (hipStream_t)stream;
+    const size_t nvox = (size_t)d.nx * d.ny * d.nz;
+    // The chip holds 768 of these workgroups at a time: with fewer tiles the
+    // records are cut into chunks of at least two per phase.  The packed
+    // densities cost 16 bytes of traffic per voxel and save one of two loads per
+    // step, worth it from about one march per 16 voxels on.
+    int chunks = 1;
+    while (chunks < 64 && tiles * chunks < 2048 && n_rec >= (int64_t)chunks * 4 * kPhases)
+        chunks *= 2;
+    const size_t npad = (size_t)(d.nx + 2) * (d.ny + 2) * (d.nz + 2);
+    const bool pack = npad < ((size_t)1 << 29) && (size_t)n_rec * npix >= nvox / 16;
+    const size_t vb = pack ? npad * sizeof(float2) : 0;
+    const size_t pb = chunks > 1 ? (size_t)chunks * npix * sizeof(float) : 0;
+    // both live in the library's buffer; under stream capture (where that
+    // buffer can neither grow nor be waited for) and where it cannot be had
+    // the marches read the caller's volumes and one workgroup takes all records
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    ScratchLease lease;
+    bool leased = false;
+    if (vb + pb > 0 && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+        cap == hipStreamCaptureStatusNone) {
+        leased = scratch_acquire(vb + pb, st, lease) == hipSuccess;
+        if (!leased) {
+            (void)hipGetLastError();
+            (void)scratch_release(st, lease);
+        }
+    }
+    const dim3 block(kPixTile * kPhases);
+    if (leased) {
+        float *part = (float *)((char *)lease.ptr + vb);
+        if (pack) {
+            A.two = (const float2 *)lease.ptr;
+            hipLaunchKernelGGL(k_pack_two, dim3((unsigned)((npad + kT - 1) / kT)), dim3(kT), 0, st,
+                               A.G, (float2 *)lease.ptr);
+        }
+        A.chunks = chunks;
+        A.out = chunks > 1 ? part : out;
+        if (pack)
+            hipLaunchKernelGGL(k_scatter_integrate<true>, dim3(tiles, chunks), block, 0, st, A);
+        else
+            hipLaunchKernelGGL(k_scatter_integrate<false>, dim3(tiles, chunks), block, 0, st, A);
+        if (chunks > 1)
+            hipLaunchKernelGGL(k_sum_chunks, dim3((npix + kT - 1) / kT), dim3(kT), 0, st, npix,
+                               chunks, (const float *)part, out);
+        const hipError_t e = hipGetLastError(), r = scratch_release(st, lease);
+        return scat_done(e != hipSuccess ? e : r);
+    }
+    hipLaunchKernelGGL(k_scatter_integrate<false>, dim3(tiles), block, 0, st, A);
     return scat_done(hipGetLastError());
 }
