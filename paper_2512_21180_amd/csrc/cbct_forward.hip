@@ -33,10 +33,17 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxR = 8;       // rays per thread
+// Planes whose boxes are loaded ahead (two: 7.83 ms against 7.82, 11 registers more).
+constexpr int kPlanes = 1;
+// Rays whose LDS reads run ahead of the arithmetic.  With all eight rays' reads
+// first (as the compiler orders them when nothing holds it) a wave's reads
+// leave in a burst that keeps the others' waiting, and take 100 registers:
+// clinical forward 9.6 ms; 8.11 one ray ahead, 8.13 two, 8.21 three, 8.35 four
+// (at five waves per SIMD).
+constexpr int kAhead = 1;
 
-constexpr int kQS = 65;        // LDS row stride (floats): box rows are <= 64 wide
+constexpr int kQS = 68;        // LDS row stride (floats): box rows are <= 64 wide
 constexpr int kMaxRows = 32;   // box rows (z) per plane
-constexpr int kSlots = kMaxRows / 4;
 constexpr int kBoxChunk = 256; // planes whose boxes are tabulated at a time
 static_assert(kBoxChunk == kThreads, "the box table is filled one plane per thread");
 // LDS: two staging boxes, then the box table (one int4 per plane of a chunk)
@@ -48,27 +55,24 @@ constexpr size_t kFwdLds = 2 * (size_t)kMaxRows * kQS * sizeof(float) + kBoxChun
 //
 // On plane p the box spans in-plane indices [qlo, qlo + qw) and z indices
 // [klo, klo + kw), from the corner rays' crossings widened by one voxel for
-// rounding; wave w stages rows w, w + 4, ... with lane l holding column l,
-// so each row is one load per lane.
+// rounding; a wave stages four rows per load, a quad of voxels per lane.
 // tub: log2 of the tile width (6 or 5).  RC > 0 fixes R at compile time (the
 // plans' usual 8 rays per thread): the per-ray tests then vanish, which
 // matters because the sweep issues nearly as many scalar as vector
 // instructions and a SIMD takes one of each per four cycles.
-// vt: the volume with x and y swapped ([nz][nx][ny]) or null.  Tiles that
+// v: the volume in FP32, vt: the same with x and y swapped ([nz][nx][ny]).  Tiles that
 // sweep x planes read their boxes from it, so a box row (fixed z, in-plane
 // index y) is contiguous; in the volume itself its voxels lie nx apart, a
-// cache line each (the clinical forward: 12.2 ms reading them strided,
-// 8.8 ms from the transposed copy).
-template <class VS, class SS, int RC = 0>
+// cache line each (the clinical forward, an earlier build: 12.2 ms reading
+// them strided, 8.8 ms from the transposed copy).
+template <class SS, int RC = 0>
 __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, int R_rt, int tub,
-                           const typename VS::T *__restrict__ v,
-                           const typename VS::T *__restrict__ vt,
+                           const float *__restrict__ v, const float *__restrict__ vt,
                            typename SS::T *__restrict__ sino, float *lds)
 {
     const int R = RC > 0 ? RC : R_rt;
     const int tid = threadIdx.x;
-    // the wave index is uniform: the staging's slot ranges below are
-    // scalar, so their tests are scalar branches
+    // the wave index is uniform: the staging's slot tests below are scalar
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int uc = lane & ((1 << tub) - 1);                   // tile column
     const int row0 = ((w << (6 - tub)) + (lane >> tub)) * R;  // first tile row
@@ -96,12 +100,9 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
 
     const bool xp = T.cls == 0;
     const int nq = xp ? g.ny : g.nx;
-    const bool tr = xp && vt != nullptr;   // x planes from the transposed copy
-    const typename VS::T *src = tr ? vt : v;
-    const int sp = xp ? (tr ? g.ny : 1) : g.nx;   // plane stride
-    const int sq = xp && !tr ? g.nx : 1;         // in-plane stride
-    const int sk = g.nx * g.ny;        // z stride (volumes have < 2^31 voxels)
-
+    const float *src = xp ? vt : v;    // rows of nq voxels between zero pads
+    const int sp = sweep_pitch(nq);    // plane stride
+    const int sk = sp * (xp ? g.nx : g.ny);   // z stride
     struct Box {
         int qlo, klo, qw, kw;
     };
@@ -132,86 +133,63 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
         b.kw = __builtin_amdgcn_readfirstlane(v.w);
         return b;
     };
-    // stored values stay raw until the LDS store, so the loads of the next
-    // plane stay in flight while this plane is summed
-    using Raw = typename VS::Raw;
-    // Slot s of wave w holds box row w + 4 s, z index k0 + 4 s with
-    // k0 = klo + w; the wave loads the slots inside the box rows (a uniform
-    // count).  FP32 loads go through a buffer resource over the volume,
-    // whose range check returns zero for everything outside it: slots below
-    // z index 0 (their 32-bit offsets wrap past the end; the plan keeps the
-    // volume with 64 more planes under 4 GiB), slots past the top, and lanes
-    // outside the volume in plane (their first offset is set to the end).
-    const uint32_t vbytes = (uint32_t)sk * (uint32_t)g.nz * (uint32_t)sizeof(typename VS::T);
+    // A wave's load takes four box rows of up to 16 quads of voxels (row
+    // 4 s + lane / 16, quad lane % 16 for slot s; wave w has slots w and w + 4),
+    // so a plane's box takes five loads and five LDS stores of 16 bytes a lane
+    // in all, where a load per row took four times as many.  A quad that
+    // straddles the volume's edge reads the row's zero pad; lanes
+    // outside the volume or the box get an offset past the end, for which the
+    // buffer resource returns zero.  The values stay in registers until the
+    // LDS store, so the loads of the next plane stay in flight while this
+    // plane is summed.
+    const uint32_t vbytes = (uint32_t)sk * (uint32_t)g.nz * (uint32_t)sizeof(float);
     const __amdgpu_buffer_rsrc_t vres =
         __builtin_amdgcn_make_buffer_rsrc((void *)src, (short)0, (int)vbytes, kBufferWord3);
-    const uint32_t step = 4u * (uint32_t)sk * (uint32_t)sizeof(typename VS::T);
-    auto fetch = [&](int p, const Box &b, Raw (&st)[kSlots]) {
-        const int q = b.qlo + lane;
-        const bool qin = lane < b.qw && (unsigned)q < (unsigned)nq;
-        if constexpr (sizeof(typename VS::T) == 4) {
-            const int n_sl = (b.kw - w + 3) >> 2;
-            // modular: exact for slots inside the volume
-            const uint32_t off0 =
-                qin ? (__umul24((uint32_t)q, (uint32_t)sq) + (uint32_t)p * (uint32_t)sp +
-                       (uint32_t)(b.klo + w) * (uint32_t)sk) *
-                          (uint32_t)sizeof(typename VS::T)
-                    : vbytes;
+    const int quad = 4 * (lane & 15), srow = 4 * w + (lane >> 4);
+    const uint32_t lane_off = 4u * ((uint32_t)srow * (uint32_t)sk + (uint32_t)quad + kSweepPad);
+    auto fetch = [&](int p, const Box &b, float4 (&st)[2]) {
+        const bool qin = quad < b.qw && (unsigned)(b.qlo + quad + 3) < (unsigned)(nq + 3);
+        // modular: exact for quads inside the volume
+        const uint32_t off0 = lane_off + 4u * ((uint32_t)b.qlo + (uint32_t)p * (uint32_t)sp +
+                                               (uint32_t)b.klo * (uint32_t)sk);
 #pragma unroll
-            for (int s = 0; s < kSlots; ++s)
-                if (s < n_sl)
-                    st[s] = VS::buf_at(vres, off0 + (uint32_t)s * step);
-        } else {
-            // 16-bit volumes: masked global loads (slots inside the box rows
-            // and the volume as a wave-uniform bit mask, the lane test one
-            // exec region): 16-bit buffer loads staged them more slowly
-            const int k0 = b.klo + w;
-            const int s_lo = k0 >= 0 ? 0 : (3 - k0) >> 2;
-            const int s_hi = min((b.kw - w + 3) >> 2, (g.nz - k0 + 3) >> 2);
-            const uint32_t live =
-                s_hi > s_lo ? ((1u << s_hi) - 1u) & ~((1u << s_lo) - 1u) : 0u;
-            const uint32_t off0 =
-                (uint32_t)(q * sq + p * sp + k0 * sk) * (uint32_t)sizeof(typename VS::T);
-#pragma unroll
-            for (int s = 0; s < kSlots; ++s)
-                st[s] = Raw(0);
-            if (qin) {
-#pragma unroll
-                for (int s = 0; s < kSlots; ++s)
-                    if (live & (1u << s))
-                        st[s] = VS::raw_at(src, off0 + (uint32_t)s * step);
+        for (int i = 0; i < 2; ++i)
+            if (i == 0 || b.kw > 4 * w + 16) {
+                const bool in = qin && (unsigned)(b.klo + srow + 16 * i) < (unsigned)g.nz;
+                // the offset stays alive past its load (the empty asm), so it
+                // cannot be formed in the load's own registers: those may
+                // still await an earlier load, and the wave would then wait
+                // for all loads in flight here
+                const uint32_t off = in ? off0 + (uint32_t)i * 64u * (uint32_t)sk : vbytes;
+                const auto d = __builtin_amdgcn_raw_buffer_load_b128(vres, (int)off, 0, 0);
+                st[i] = make_float4(__uint_as_float(d[0]), __uint_as_float(d[1]),
+                                    __uint_as_float(d[2]), __uint_as_float(d[3]));
+                asm volatile("" ::"v"(off));
             }
-        }
     };
 
     __syncthreads();   // the previous work item's readers of lds are done
     int p = T.p_lo, base = T.p_lo;
     fill_boxes(base);
     __syncthreads();
-    Box nb{0, 0, 0, 0};
-    Raw stage[kSlots];
-    if (p <= T.p_hi) {
-        nb = box_of(p, base);
-        fetch(p, nb, stage);
-    }
-    for (; p <= T.p_hi; ++p) {
+    // One plane: store its box (in registers since kPlanes planes ago), start
+    // the loads of the plane kPlanes later into the same registers, sum the rays.
+    auto plane = [&](int p, Box &bx, float4 (&stage)[2]) {
         float *buf = lds + (p & 1) * (kMaxRows * kQS);
-        const Box cb = nb;
-        // the slots inside the box rows, as a wave-uniform bit mask
-        const uint32_t rows = (1u << ((cb.kw - w + 3) >> 2)) - 1u;
-#pragma unroll
-        for (int s = 0; s < kSlots; ++s)
-            if (rows & (1u << s))
-                buf[(w + 4 * s) * kQS + lane] = VS::wide(stage[s]);
+        const Box cb = bx;
+        float *dst = buf + srow * kQS + quad;
+        *(float4 *)dst = stage[0];
+        if (cb.kw > 4 * w + 16)
+            *(float4 *)(dst + 16 * kQS) = stage[1];
         __syncthreads();
-        if (p < T.p_hi) {
-            if (p + 1 - base == kBoxChunk) {   // uniform: next chunk of boxes
+        if (p + kPlanes <= T.p_hi) {
+            if (p + kPlanes - base == kBoxChunk) {   // uniform: next chunk of boxes
                 base += kBoxChunk;
                 fill_boxes(base);   // every reader of the old chunk is past the barrier
                 __syncthreads();
             }
-            nb = box_of(p + 1, base);
-            fetch(p + 1, nb, stage);
+            bx = box_of(p + kPlanes, base);
+            fetch(p + kPlanes, bx, stage);
         }
         const float fp = (float)p;
         const float q = fmaf(fp, c.ps, c.pb);
@@ -221,32 +199,54 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
         // row, klo, lies at its position in box row 0)
         const int colz =
             (int)(lds_addr(buf) + 4u * (uint32_t)((int)qf - cb.qlo)) - cb.klo * (4 * kQS);
-        // all rays' reads first, then their arithmetic: the reads of the
-        // rays overlap instead of each ray waiting for its own
+        // ray r's arithmetic runs while the reads of the next kAhead rays are
+        // in flight; the scheduling barriers keep that order
         float wk[kMaxR], v00[kMaxR], v10[kMaxR], v01[kMaxR], v11[kMaxR];
+        auto read = [&](int r) {
+            // z index k of the ray on this plane: its weight is the
+            // exact fraction of k, its row address one floor conversion
+            // and one multiply-add (every ray's floor(k) lies in the box
+            // rows [klo, klo + kw - 1), so the address is inside the box)
+            const float k = fmaf(fp, ks[r], kb[r]);
+            wk[r] = __builtin_amdgcn_fractf(k);
+            const lds_float *row = lds_ptr((uint32_t)mad_i24(floor_i32(k), 4 * kQS, colz));
+            v00[r] = row[0];
+            v10[r] = row[1];
+            v01[r] = row[kQS];
+            v11[r] = row[kQS + 1];
+        };
+#pragma unroll
+        for (int r = 0; r < kAhead; ++r)
+            if (r < R)
+                read(r);
 #pragma unroll
         for (int r = 0; r < kMaxR; ++r) {
-            if (r < R) {
-                // z index k of the ray on this plane: its weight is the
-                // exact fraction of k, its row address one floor conversion
-                // and one multiply-add (every ray's floor(k) lies in the box
-                // rows [klo, klo + kw - 1), so the address is inside the box)
-                const float k = fmaf(fp, ks[r], kb[r]);
-                wk[r] = __builtin_amdgcn_fractf(k);
-                const lds_float *row = lds_ptr((uint32_t)mad_i24(floor_i32(k), 4 * kQS, colz));
-                v00[r] = row[0];
-                v10[r] = row[1];
-                v01[r] = row[kQS];
-                v11[r] = row[kQS + 1];
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (r + kAhead < kMaxR && r + kAhead < R)
+                read(r + kAhead);
+            __builtin_amdgcn_sched_barrier(0);
             if (r < R) {
                 const float lo = fmaf(wq, v10[r] - v00[r], v00[r]);
                 const float hi = fmaf(wq, v11[r] - v01[r], v01[r]);
                 acc[r] += fmaf(wk[r], hi - lo, lo);
             }
+        }
+    };
+    Box nb[kPlanes];
+    float4 stage[kPlanes][2];
+#pragma unroll
+    for (int i = 0; i < kPlanes; ++i)
+        if (p + i <= T.p_hi) {
+            nb[i] = box_of(p + i, base);
+            fetch(p + i, nb[i], stage[i]);
+        }
+    while (p <= T.p_hi) {
+#pragma unroll
+        for (int i = 0; i < kPlanes; ++i) {
+            if (p > T.p_hi)
+                break;
+            plane(p, nb[i], stage[i]);
+            ++p;
         }
     }
 
@@ -283,15 +283,14 @@ struct SweepArgs {
     int R, tub;   // rays per thread, log2 of the tile width
 };
 
-// At most five waves per SIMD: with more resident tiles the planes' boxes of
-// different tiles compete for the caches (clinical case, earlier build:
-// 15.3 ms at six waves, 13.5 ms at five, 14.5 ms at four).  At the current
-// register count the occupancy is four; five would need 96 VGPRs, which
-// spills.
-template <class VS, class SS, int RC>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 5)))
-forward_sweep(SweepArgs A, const typename VS::T *__restrict__ vol,
-              const typename VS::T *__restrict__ volt, typename SS::T *__restrict__ sino)
+// Seven waves per SIMD (72 registers; the LDS of seven workgroups fits a CU).
+// The sweep is bound by VALU issue (5.2e9 wave instructions, the whole
+// of its 7.7 ms), so more waves only fill the gaps between dependent reads:
+// clinical forward 8.06 ms at five, 7.84 at six, 7.71 at seven.
+template <class SS, int RC>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 7)))
+forward_sweep(SweepArgs A, const float *__restrict__ vol, const float *__restrict__ volt,
+              typename SS::T *__restrict__ sino)
 {
     extern __shared__ float lds[];
     // XCD-contiguous tile order: workgroups are dealt to the 8 XCDs round
@@ -303,10 +302,10 @@ forward_sweep(SweepArgs A, const typename VS::T *__restrict__ vol,
     if (T.nu_t == 0)
         return;
     const int ch = blockIdx.y;
-    const size_t nvox = (size_t)A.g.nx * A.g.ny * A.g.nz;
     const size_t nsino = (size_t)A.g.n_angles * A.g.nv * A.g.nu;
-    sweep_tile<VS, SS, RC>(A.g, T, A.R, A.tub, vol + ch * nvox, volt + ch * nvox,
-                           sino + ch * nsino, lds);
+    const size_t nv = (size_t)A.g.nz * A.g.ny * sweep_pitch(A.g.nx);
+    const size_t nt = (size_t)A.g.nz * A.g.nx * sweep_pitch(A.g.ny);
+    sweep_tile<SS, RC>(A.g, T, A.R, A.tub, vol + ch * nv, volt + ch * nt, sino + ch * nsino, lds);
 }
 
 // ---- batched forward: one launch over all (case, tile) items ----------------
@@ -315,7 +314,7 @@ struct FwdCase {
     DevGeom g;
     const TileRec *tiles;
     int R, tub, n_tiles;
-    const void *vol, *volt;   // the volume, and with x and y swapped
+    const float *vol, *volt;   // the volume, and with x and y swapped
     void *sino;
 };
 
@@ -325,8 +324,8 @@ struct BatchFwdArgs {
     FwdCase c[kMaxBatch];
 };
 
-template <class VS, class SS>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 5)))
+template <class SS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 7)))
 forward_batch(BatchFwdArgs B)
 {
     extern __shared__ float lds[];
@@ -346,11 +345,9 @@ forward_batch(BatchFwdArgs B)
     // cases with the usual rays per thread take the sweep specialised for it
     // (a uniform branch; the bits do not depend on the variant)
     if (C.R == kMaxR)
-        sweep_tile<VS, SS, kMaxR>(C.g, T, C.R, C.tub, (const typename VS::T *)C.vol,
-                                  (const typename VS::T *)C.volt, (typename SS::T *)C.sino, lds);
+        sweep_tile<SS, kMaxR>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
     else
-        sweep_tile<VS, SS>(C.g, T, C.R, C.tub, (const typename VS::T *)C.vol,
-                           (const typename VS::T *)C.volt, (typename SS::T *)C.sino, lds);
+        sweep_tile<SS>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
 }
 
 }  // namespace
@@ -362,27 +359,24 @@ hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *
     SweepArgs A{g, p.tiles, p.R, p.TU == 32 ? 5 : 6};
     const size_t lds = kFwdLds;
     dim3 grid(p.n_tiles, channels), block(kThreads);
-    // the volume with x and y swapped, in the library's device buffer, for
-    // the tiles that sweep x planes
-    const size_t nvox = (size_t)g.nx * g.ny * g.nz;
+    // the volume with x and y swapped (and in FP32), in the library's device
+    // buffer, for the tiles that sweep x planes (and for 16-bit volumes)
     ScratchLease lease;
-    hipError_t e = scratch_acquire(nvox * channels * storage_bytes(vt), s, lease);
-    if (e == hipSuccess)
-        e = dispatch_storage(vt, st, [&](auto vs, auto ss) -> hipError_t {
-            using VS = decltype(vs);
+    hipError_t e = scratch_acquire(
+        sweep_words(g.nx, g.ny, (size_t)g.nz * channels) * sizeof(float), s, lease);
+    if (e == hipSuccess) {
+        const SweepVolumes v =
+            make_sweep_volumes(vol, vt, (float *)lease.ptr, g.nx, g.ny, g.nz * channels, s);
+        e = dispatch_storage(vt, st, [&](auto, auto ss) -> hipError_t {
             using SS = decltype(ss);
-            using T = typename VS::T;
-            const T *x = (const T *)vol;
-            T *xt = (T *)lease.ptr;
-            launch_transpose_xy(x, xt, g.nx, g.ny, g.nz * channels, s);
+            auto *y = (typename SS::T *)sino;
             if (p.R == kMaxR)
-                hipLaunchKernelGGL((forward_sweep<VS, SS, kMaxR>), grid, block, lds, s, A, x, xt,
-                                   (typename SS::T *)sino);
+                hipLaunchKernelGGL((forward_sweep<SS, kMaxR>), grid, block, lds, s, A, v.vol, v.volt, y);
             else
-                hipLaunchKernelGGL((forward_sweep<VS, SS, 0>), grid, block, lds, s, A, x, xt,
-                                   (typename SS::T *)sino);
+                hipLaunchKernelGGL((forward_sweep<SS, 0>), grid, block, lds, s, A, v.vol, v.volt, y);
             return hipGetLastError();
         });
+    }
     const hipError_t r = scratch_release(s, lease);
     return e != hipSuccess ? e : r;
 }
@@ -393,35 +387,34 @@ hipError_t launch_forward_batch(int n, const cbct_geom *const *gs, const void *c
     BatchFwdArgs B{};
     B.n_cases = n;
     int items = 0;
-    size_t off[kMaxBatch], total = 0;   // the cases' transposed volumes in the library's buffer
+    size_t off[kMaxBatch], total = 0;   // words of the cases' copies in the library's buffer
     for (int i = 0; i < n; ++i) {
         const cbct_geom *g = gs[i];
         B.first[i] = items;
         B.c[i] = FwdCase{g->dev, g->fwd.tiles, g->fwd.R, g->fwd.TU == 32 ? 5 : 6,
-                         g->fwd.n_tiles, vols[i], nullptr, sinos[i]};
+                         g->fwd.n_tiles, nullptr, nullptr, sinos[i]};
         items += g->fwd.n_tiles;
         off[i] = total;
-        total += ((size_t)g->dev.nx * g->dev.ny * g->dev.nz * storage_bytes(vt) + 255) & ~(size_t)255;
+        total += (sweep_words(g->dev.nx, g->dev.ny, g->dev.nz) + 63) & ~(size_t)63;
     }
     B.first[n] = items;
     B.n_items = items;
     const int grid = (items + 7) / 8 * 8;
     ScratchLease lease;
-    hipError_t e = scratch_acquire(total, s, lease);
-    if (e == hipSuccess)
-        e = dispatch_storage(vt, st, [&](auto vs, auto ss) -> hipError_t {
-            using VS = decltype(vs);
-            using SS = decltype(ss);
-            using T = typename VS::T;
-            for (int i = 0; i < n; ++i) {
-                T *xt = (T *)((char *)lease.ptr + off[i]);
-                launch_transpose_xy((const T *)vols[i], xt, gs[i]->dev.nx, gs[i]->dev.ny,
-                                    gs[i]->dev.nz, s);
-                B.c[i].volt = xt;
-            }
-            hipLaunchKernelGGL((forward_batch<VS, SS>), dim3(grid), dim3(kThreads), kFwdLds, s, B);
+    hipError_t e = scratch_acquire(total * sizeof(float), s, lease);
+    if (e == hipSuccess) {
+        for (int i = 0; i < n; ++i) {
+            const DevGeom &d = gs[i]->dev;
+            const SweepVolumes v = make_sweep_volumes(vols[i], vt, (float *)lease.ptr + off[i],
+                                                      d.nx, d.ny, d.nz, s);
+            B.c[i].vol = v.vol;
+            B.c[i].volt = v.volt;
+        }
+        e = dispatch_storage(vt, st, [&](auto, auto ss) -> hipError_t {
+            hipLaunchKernelGGL((forward_batch<decltype(ss)>), dim3(grid), dim3(kThreads), kFwdLds, s, B);
             return hipGetLastError();
         });
+    }
     const hipError_t r = scratch_release(s, lease);
     return e != hipSuccess ? e : r;
 }

@@ -69,6 +69,12 @@ struct FwdPlan {
     const TileRec *tiles = nullptr;   // device
 };
 
+// The forward sweeps' copies of a volume: rows of n voxels between zero pads of
+// at least four, so that a quad of voxels that starts up to three below 0 or
+// ends up to three past n stays in its row.
+constexpr int kSweepPad = 4;
+__host__ __device__ inline int sweep_pitch(int n) { return (n + 2 * kSweepPad + 3) & ~3; }
+
 // Row taps the adjoint reads per voxel and column: the needed count rounded
 // up to a count its kernel is instantiated for (4..16, 18, 20, 24, 28, 32).
 __host__ __device__ inline int adj_taps_rounded(int nt)

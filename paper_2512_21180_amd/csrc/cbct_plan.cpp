@@ -253,10 +253,13 @@ void plan_host(cbct_geom *g)
     g->tiles.clear();
     TileBuild tb;
     int R = 0, TU = 64;
-    // the tiled kernel addresses one volume channel with 32-bit byte offsets,
-    // those of slots below the volume wrapping past its end (64 planes of
-    // margin)
-    const bool off32 = (uint64_t)d.nx * d.ny * (d.nz + 64) * sizeof(float) < (1ull << 32);
+    // the tiled kernels address one volume channel, and its padded copies, with
+    // 32-bit byte offsets; those of slots below the volume wrap past its end
+    // (64 planes of margin, which the channel stacks' sweep relies on)
+    const uint64_t rows = (uint64_t)d.nz * sizeof(float);
+    const bool off32 = (uint64_t)d.nx * d.ny * (d.nz + 64) * sizeof(float) < (1ull << 32) &&
+                       rows * d.ny * sweep_pitch(d.nx) < (1ull << 32) &&
+                       rows * d.nx * sweep_pitch(d.ny) < (1ull << 32);
     for (int tu : {64, 32}) {
         if (!off32)
             break;

@@ -8,6 +8,8 @@
 #include <algorithm>
 #include <cstddef>
 
+#include "cbct_storage.h"
+
 namespace cbct {
 namespace {
 
@@ -42,12 +44,77 @@ transpose_xy(const T *__restrict__ in, T *__restrict__ out, int nx, int ny, int 
     }
 }
 
+// The two FP32 copies the forward sweeps stage from: the volume as it is
+// ([z][y][pitch]) and with x and y swapped ([z][x][pitch]), rows between zero
+// pads (sweep_pitch), so that the sweeps load quads of voxels without a test
+// of their single voxels, whatever the storage.
+template <class VS>
+__global__ void __launch_bounds__(256)
+sweep_copies(const typename VS::T *__restrict__ in, float *__restrict__ wide,
+             float *__restrict__ out, int nx, int ny, int n_slices)
+{
+    __shared__ float tile[32][33];
+    const int px = sweep_pitch(nx), py = sweep_pitch(ny);
+    // tiles cover the padded rows of both copies
+    const int tx = (px + 31) >> 5;
+    const int x0 = (blockIdx.x % tx) * 32 - kSweepPad, y0 = (blockIdx.x / tx) * 32 - kSweepPad;
+    const int lx = threadIdx.x & 31, ly = threadIdx.x >> 5;   // 32 x 8
+    for (int sl = blockIdx.y; sl < n_slices; sl += gridDim.y) {
+        __syncthreads();   // the previous slice's readers of the tile are done
+#pragma unroll
+        for (int j = ly; j < 32; j += 8) {
+            const int x = x0 + lx, y = y0 + j;
+            float v = 0.0f;
+            if ((unsigned)x < (unsigned)nx && (unsigned)y < (unsigned)ny)
+                v = VS::wide(VS::raw(in, ((size_t)sl * ny + y) * nx + x));
+            if ((unsigned)y < (unsigned)ny && x + kSweepPad < px)
+                wide[((size_t)sl * ny + y) * px + x + kSweepPad] = v;
+            tile[j][lx] = v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = ly; j < 32; j += 8) {
+            const int y = y0 + lx, x = x0 + j;
+            if ((unsigned)x < (unsigned)nx && y + kSweepPad < py)
+                out[((size_t)sl * nx + x) * py + y + kSweepPad] = tile[lx][j];
+        }
+    }
+}
+
 // Launch transpose_xy over n_slices slices of nx x ny elements.
 template <class T>
 inline void launch_transpose_xy(const T *in, T *out, int nx, int ny, int n_slices, hipStream_t s)
 {
     const dim3 grid(((nx + 31) / 32) * ((ny + 31) / 32), std::min(n_slices, 65535));
     hipLaunchKernelGGL((transpose_xy<T>), grid, dim3(256), 0, s, in, out, nx, ny, n_slices);
+}
+
+// FP32 words of the two copies of n_slices slices, and the copies made in `buf`.
+inline size_t sweep_words(int nx, int ny, size_t n_slices)
+{
+    return n_slices * ((size_t)ny * sweep_pitch(nx) + (size_t)nx * sweep_pitch(ny));
+}
+
+struct SweepVolumes {
+    const float *vol, *volt;
+};
+
+inline SweepVolumes make_sweep_volumes(const void *vol, cbct_dtype t, float *buf, int nx, int ny,
+                                       int n_slices, hipStream_t s)
+{
+    float *wide = buf, *out = buf + (size_t)n_slices * ny * sweep_pitch(nx);
+    const dim3 grid(((sweep_pitch(nx) + 31) / 32) * ((sweep_pitch(ny) + 31) / 32),
+                    std::min(n_slices, 65535));
+    if (t == CBCT_F32)
+        hipLaunchKernelGGL(sweep_copies<F32>, grid, dim3(256), 0, s, (const F32::T *)vol, wide, out,
+                           nx, ny, n_slices);
+    else if (t == CBCT_BF16)
+        hipLaunchKernelGGL(sweep_copies<BF16>, grid, dim3(256), 0, s, (const BF16::T *)vol, wide,
+                           out, nx, ny, n_slices);
+    else
+        hipLaunchKernelGGL(sweep_copies<F16>, grid, dim3(256), 0, s, (const F16::T *)vol, wide, out,
+                           nx, ny, n_slices);
+    return {wide, out};
 }
 
 }  // namespace
