@@ -43,6 +43,16 @@
 // zeros (a run that would leave the window starts lower instead).  The
 // window is stored column-major, so a run is consecutive LDS words read two
 // at a time with immediate offsets in a fully unrolled sequence.
+//
+// Angles: one wave lists the next angles at which the window meets the panel
+// (32 tested at once, one per lane); of every four listed angles each wave
+// finds one's column ranges, which all waves use; and where four windows fit
+// in a workgroup's share of the LDS they are staged together, one round trip to memory
+// and two barriers for four angles.  When every wave found every
+// angle's ranges and each angle was tested, staged and gathered by itself the
+// clinical adjoint took 13.98 ms (now 12.70), the 64^3 one 220 us (150), four
+// channels of 128^3 x 180 x 256^2 6.0 ms (4.7).  Bound by VALU issue in the taps
+// where windows are tall, by the per-column set-up where runs are short.
 
 #include <hip/hip_runtime.h>
 
@@ -65,9 +75,11 @@ constexpr bool adj_tall(int KV, int HS) { return KV == 4 && HS >= 4 * kStageRows
 struct BrickArgs {
     DevGeom g;
     const BrickWin *wins;  // [n_angles][nby][nbx] panel windows
-    int W, H, HS;          // window columns and rows, LDS column stride
+    int W, H, HS;          // window columns (even) and rows, LDS column stride
     int nbx, nby, nbz;
     int KV;                // voxels per lane along z (bricks 8 x 7 x 4 KV)
+    int gw;                // panel windows staged at a time: 4, 2 or 1
+    int area;              // LDS words of the windows
     float rbias;           // 1 - adj_start_delta(nv)
 };
 
@@ -88,18 +100,47 @@ __device__ inline void project_xy(const DevGeom &g, float inv_du, float c, float
     u = fmaf(fmaf(lam, fmaf(-s, x, c * y), -g.off_u), inv_du, g.cu);
 }
 
+// One angle of a brick's work list: the angles at which the brick's window
+// meets the panel, in order.
+struct AngleEnt {
+    int a;
+    uint32_t u01;       // window columns U0 | U1 << 16
+    int V0;             // first window row
+    uint32_t hn;        // window rows | row taps << 16
+    int x_lo, x_hi;     // columns sampled on x planes
+    float lmin, lmax;   // extreme source-panel scales of the brick's support
+};
+static_assert(sizeof(AngleEnt) == 32, "AngleEnt layout");
+constexpr int kListAngles = 32;   // angles listed at a time
+constexpr int kGroup = 4;         // angles whose column ranges are found at a time
+
+__device__ inline AngleEnt uniform_ent(const AngleEnt &e)
+{
+    AngleEnt r;
+    r.a = __builtin_amdgcn_readfirstlane(e.a);
+    r.u01 = __builtin_amdgcn_readfirstlane(e.u01);
+    r.V0 = __builtin_amdgcn_readfirstlane(e.V0);
+    r.hn = __builtin_amdgcn_readfirstlane(e.hn);
+    r.x_lo = __builtin_amdgcn_readfirstlane(e.x_lo);
+    r.x_hi = __builtin_amdgcn_readfirstlane(e.x_hi);
+    r.lmin = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(e.lmin)));
+    r.lmax = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(e.lmax)));
+    return r;
+}
+
 // Inputs of one angle's gather for one lane.
 struct GatherIn {
     const DevGeom &g;
-    const AngRec &ar;
+    int x_lo, x_hi;
     const float *yt;
     const float4 *cr;
-    int HS, U0, U1, V0;
+    int HS, U0, V0;
     int VS1;   // largest run start: max(V1 - NT + 1, V0), so a run ends in the window
     int k0;
     int pl[2], sg[2];   // per sampling axis (0: x planes, 1: y planes): this lane's
                         // plane and in-plane segment; pl < 0: no work on that axis
-    float inv_du, inv_rvs;
+    uint2 range;        // per axis the lane's columns, from U0: first | last << 16
+    float inv_rvs;
     float rbias;        // 1 - delta: run start floor(v_c + 1 - delta)
 };
 
@@ -127,10 +168,9 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][
                                              float (&hi)[2][KV])
 {
     const DevGeom &g = in.g;
-    const AngRec &ar = in.ar;
     const int HS = in.HS, U0 = in.U0, V0 = in.V0, VS1 = in.VS1;
     const int k0 = in.k0;
-    const float inv_du = in.inv_du, inv_rvs = in.inv_rvs;
+    const float inv_rvs = in.inv_rvs;
     const float *yt = in.yt;
     const float4 *cr = in.cr;
     // Per voxel n: the row v_c where a ray with parameter t crosses z index
@@ -148,46 +188,11 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][
     const float V0f = (float)V0, VS1f = (float)VS1;
 #pragma unroll
     for (int cls = 0; cls < 2; ++cls) {
-        // this axis has columns at this angle (uniform) and this lane a segment
-        if (cls == 0 ? ar.x_lo >= ar.x_hi : (ar.x_lo == 0 && ar.x_hi == g.nu))
-            continue;
-        if (in.pl[cls] < 0)
-            continue;
+        const uint32_t range = cls == 0 ? in.range.x : in.range.y;
         const float fp = (float)in.pl[cls], sf = (float)in.sg[cls];
-        int c_lo, c_hi;   // this axis' columns
-        float u1, u2, lam;
-        if (cls == 0) {   // x planes: plane i, segment [s, s + 1) in y
-            c_lo = ar.x_lo;
-            c_hi = ar.x_hi - 1;
-            const float xp = centre_x(g, fp), ya = centre_y(g, sf);
-            project_xy(g, inv_du, ar.c, ar.s, xp, ya, u1, lam);
-            project_xy(g, inv_du, ar.c, ar.s, xp, ya + g.vy, u2, lam);
-        } else {          // y planes: plane j, segment [s, s + 1) in x
-            c_lo = 0;
-            c_hi = g.nu - 1;
-            const float yp = centre_y(g, fp), xa = centre_x(g, sf);
-            project_xy(g, inv_du, ar.c, ar.s, xa, yp, u1, lam);
-            project_xy(g, inv_du, ar.c, ar.s, xa + g.vx, yp, u2, lam);
-        }
-        // The segment's columns lie between the projections of its two
-        // edges (within rounding, far below a column): trim the candidate
-        // range's ends to columns that are members by the exact test (the
-        // membership test below keeps the partition exact in any case).
-        int ul = max(max((int)floorf(fminf(u1, u2)), c_lo), U0);
-        int uh = min(min((int)ceilf(fmaxf(u1, u2)), c_hi), in.U1);
-        auto member = [&](int u) {
-            if (cls == 1 && u >= ar.x_lo && u < ar.x_hi)
-                return false;
-            const float4 cq = cr[u - U0];
-            const float f = fmaf(fp, cq.y, cq.x) - sf;
-            return f >= 0.0f && f < 1.0f;
-        };
-        while (ul <= uh && !member(ul))
-            ++ul;
-        while (uh > ul && !member(uh))
-            --uh;
-        for (int u = ul; u <= uh; ++u) {
-            if (cls == 1 && u >= ar.x_lo && u < ar.x_hi)
+        const int uh = U0 + (int)(range >> 16);
+        for (int u = U0 + (int)(range & 0xffffu); u <= uh; ++u) {
+            if (cls == 1 && u >= in.x_lo && u < in.x_hi)
                 continue;   // those columns are sampled on x planes
             const float4 cq = cr[u - U0];
             const float f = fmaf(fp, cq.y, cq.x) - sf;
@@ -231,6 +236,102 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][
     }
 }
 
+// The columns whose rays cross this lane's planes inside its segments at one
+// angle, per sampling axis as first | last << 16 counted from U0 (none: last
+// below first), from the window's column records cr.  All four waves of a brick
+// need the same ranges, so each finds them for one angle of a group.
+__device__ inline uint2 column_ranges(const DevGeom &g, const AngleEnt &e, const int (&pl)[2],
+                                      const int (&sg)[2], float inv_du, const float4 *cr)
+{
+    const AngRec ar = g.angs[e.a];
+    const int U0 = (int)(e.u01 & 0xffffu), U1 = (int)(e.u01 >> 16);
+    uint32_t out[2];
+#pragma unroll
+    for (int cls = 0; cls < 2; ++cls) {
+        out[cls] = 1u;
+        // this axis has columns at this angle (uniform) and this lane a segment
+        if (cls == 0 ? e.x_lo >= e.x_hi : (e.x_lo == 0 && e.x_hi == g.nu))
+            continue;
+        if (pl[cls] < 0)
+            continue;
+        const float fp = (float)pl[cls], sf = (float)sg[cls];
+        int c_lo, c_hi;   // this axis' columns
+        float u1, u2, lam;
+        if (cls == 0) {   // x planes: plane i, segment [s, s + 1) in y
+            c_lo = e.x_lo;
+            c_hi = e.x_hi - 1;
+            const float xp = centre_x(g, fp), ya = centre_y(g, sf);
+            project_xy(g, inv_du, ar.c, ar.s, xp, ya, u1, lam);
+            project_xy(g, inv_du, ar.c, ar.s, xp, ya + g.vy, u2, lam);
+        } else {          // y planes: plane j, segment [s, s + 1) in x
+            c_lo = 0;
+            c_hi = g.nu - 1;
+            const float yp = centre_y(g, fp), xa = centre_x(g, sf);
+            project_xy(g, inv_du, ar.c, ar.s, xa, yp, u1, lam);
+            project_xy(g, inv_du, ar.c, ar.s, xa + g.vx, yp, u2, lam);
+        }
+        // The segment's columns lie between the projections of its two
+        // edges (within rounding, far below a column): trim the candidate
+        // range's ends to columns that are members by the exact test (the
+        // membership test in the gather keeps the partition exact in any case).
+        int ul = max(max((int)floorf(fminf(u1, u2)), c_lo), U0);
+        int uh = min(min((int)ceilf(fmaxf(u1, u2)), c_hi), U1);
+        auto member = [&](int u) {
+            if (cls == 1 && u >= e.x_lo && u < e.x_hi)
+                return false;
+            const float4 cq = cr[u - U0];
+            const float f = fmaf(fp, cq.y, cq.x) - sf;
+            return f >= 0.0f && f < 1.0f;
+        };
+        while (ul <= uh && !member(ul))
+            ++ul;
+        while (uh > ul && !member(uh))
+            --uh;
+        if (ul <= uh)
+            out[cls] = (uint32_t)(ul - U0) | (uint32_t)(uh - U0) << 16;
+    }
+    return make_uint2(out[0], out[1]);
+}
+
+// The column records of one angle's window, by one wave.
+__device__ inline void stage_columns(const DevGeom &g, const AngleEnt &e, int lane, float4 *cr)
+{
+    const int U0 = (int)(e.u01 & 0xffffu), U1 = (int)(e.u01 >> 16);
+    for (int u = U0 + lane; u <= U1; u += 64) {
+        const ColRec col = g.cols[(size_t)e.a * g.nu + u];
+        cr[u - U0] = make_float4(col.pb, col.ps, col.t0, col.tau);
+    }
+}
+
+// Stage one angle's panel window into short columns: SB rows of loads in
+// flight per lane.  Windows of up to 32 columns (HALF) put two rows on a
+// wave's lanes.  Rows past Hs (zeros) that would leave the column go to row
+// HS - 1, a spare row no tap reads (HS > H >= Hs).
+template <int SB, bool HALF>
+__device__ __forceinline__ void stage_short(const DevGeom &g, __amdgpu_buffer_rsrc_t rows, int U0,
+                                            int Wc, int Hs, int HS, int w, int lane, float *yt)
+{
+    constexpr int kRows = HALF ? 8 : 4;   // rows of one load of the four waves
+    const int row_bytes = 4 * g.nu;
+    const int r0 = HALF ? 2 * w + (lane >> 5) : w;
+    for (int uu = HALF ? lane & 31 : lane; uu < Wc; uu += 64) {
+        float *dst = yt + (size_t)uu * HS;
+        for (int v = 0; v < Hs; v += kRows * SB) {
+            int off = 4 * (U0 + uu) + (v + r0) * row_bytes;
+            asm volatile("" : "+v"(off));   // one register (see gather_brick)
+            float val[SB];
+#pragma unroll
+            for (int jj = 0; jj < SB; ++jj)
+                val[jj] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(
+                               rows, off + kRows * jj * row_bytes, 0, 0));
+#pragma unroll
+            for (int jj = 0; jj < SB; ++jj)
+                dst[min(v + r0 + kRows * jj, HS - 1)] = val[jj];
+        }
+    }
+}
+
 // Stage one angle's panel window into a tall column layout (HS >= 4 SB):
 // Wc columns (from U0) x Hs rows of the ds-weighted projection, whose rows
 // V0 .. V1 the buffer resource `rows` holds, into yt, column-major with
@@ -241,19 +342,13 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][
 // previous batch again, with the same values), so its stores take immediate
 // offsets from one address.
 template <int SB>
-__device__ __forceinline__ void stage_tall(const DevGeom &g, int a, __amdgpu_buffer_rsrc_t rows,
-                                           int U0, int Wc, int Hs, int HS, int w, int lane,
-                                           float *yt, float4 *cr)
+__device__ __forceinline__ void stage_tall(const DevGeom &g, __amdgpu_buffer_rsrc_t rows, int U0,
+                                           int Wc, int Hs, int HS, int w, int lane, float *yt)
 {
     const int row_bytes = 4 * g.nu;
     const int top = HS - 1 - 4 * (SB - 1);   // >= 3 in tall columns
     const int vtop = top - ((top - w) & 3);  // largest start = w mod 4
     for (int uu = lane; uu < Wc; uu += 64) {
-        float4 ctab;   // one wave writes the column table (see gather_brick)
-        if (w == 0) {
-            const ColRec col = g.cols[(size_t)a * g.nu + U0 + uu];
-            ctab = make_float4(col.pb, col.ps, col.t0, col.tau);
-        }
         const int cb = 4 * (U0 + uu);   // byte offset of the column in a row
         float *dst = yt + (size_t)uu * HS;
         for (int vv0 = w; vv0 < Hs; vv0 += 4 * SB) {
@@ -270,8 +365,6 @@ __device__ __forceinline__ void stage_tall(const DevGeom &g, int a, __amdgpu_buf
             for (int jj = 0; jj < SB; ++jj)
                 d[4 * jj] = val[jj];
         }
-        if (w == 0)
-            cr[uu] = ctab;
     }
 }
 
@@ -292,9 +385,10 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
     constexpr int kBK = 4 * KV;
     constexpr int kSB = kStageRows;
     const DevGeom &g = A.g;
-    const int HS = A.HS;
-    float *yt = lds;                                    // ds-weighted panel window
-    float4 *cr = (float4 *)(lds + (size_t)A.W * HS);    // [W] (pb, ps, t0, tau)
+    const int HS = A.HS, win = A.W * (HS + 4);          // words of one window and its columns
+    uint2 *ranges = (uint2 *)(lds + A.area);            // [kGroup][64]
+    AngleEnt *list = (AngleEnt *)(ranges + kGroup * 64);
+    int *listed = (int *)(list + kListAngles);
 
     const int bx = b % A.nbx, by = (b / A.nbx) % A.nby, bz = b / (A.nbx * A.nby);
 
@@ -302,12 +396,12 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i0 = bx * kAdjBI, j0 = by * kAdjBJ;
     const int k0 = bz * kBK + w * KV;
-    int pl0 = i0 + (lane & 7), sg0 = j0 - 1 + (lane >> 3);
-    int pl1 = j0 + lane / 9, sg1 = i0 - 1 + lane % 9;
-    if (pl0 >= g.nx || sg0 >= g.ny)
-        pl0 = -1;
-    if (lane >= 63 || pl1 >= g.ny || sg1 >= g.nx)
-        pl1 = -1;
+    int pl[2] = {i0 + (lane & 7), j0 + lane / 9};
+    const int sg[2] = {j0 - 1 + (lane >> 3), i0 - 1 + lane % 9};
+    if (pl[0] >= g.nx || sg[0] >= g.ny)
+        pl[0] = -1;
+    if (lane >= 63 || pl[1] >= g.ny || sg[1] >= g.nx)
+        pl[1] = -1;
 
     // z extent of the brick's support (voxel centres +- one pitch), uniform
     const int kz0 = bz * kBK, kz1 = min(kz0 + kBK, g.nz) - 1;
@@ -330,51 +424,27 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
             hi[c][n] = 0.0f;
         }
 
-    __syncthreads();   // the previous work item's readers of lds are done
-    for (int a = 0; a < g.n_angles; ++a) {
-        // ---- panel window of the brick (uniform): columns and row taps from
-        // the table, rows from the extreme source-panel scales (positive) at
-        // the support's lowest and highest z
-        const BrickWin bw = wcol[(size_t)a * wstep];
-        const int U0 = (int)(bw.u01 & 0xffffu);
-        const int U1 = min((int)(bw.u01 >> 16), U0 + A.W - 1);
-        if (U0 > U1)
-            continue;
-        const float lmin = bw.lmin, lmax = bw.lmax;
-        const float vmin = fmaf(fminf(lmin * zs0, lmax * zs0) - g.off_v, inv_dv, g.cv);
-        const float vmax = fmaf(fmaxf(lmin * zs1, lmax * zs1) - g.off_v, inv_dv, g.cv);
-        const int V0 = max((int)floorf(vmin) - 2, 0);
-        const int V1 = min(min((int)ceilf(vmax) + 2, g.nv - 1), V0 + A.H - 1);
-        if (V0 > V1)
-            continue;
-        const int NT = bw.nt;
-        const AngRec ar = g.angs[a];
-        const int Wc = U1 - U0 + 1;
+    // One angle's window: rows V0 .. V1 of the ds-weighted projection through a
+    // buffer resource holding exactly those rows: the range check returns
+    // zero for every row past V1 (the window's zero rows and a batch's rows
+    // past Hs) without touching memory, so no load needs a test of its own.
+    // Byte offsets within the rows are 32-bit (nv nu < 2^24).  The loads of a batch
+    // of rows are issued before any of them is used, so their latencies
+    // overlap instead of adding up row after row, and every store is
+    // unconditional, so no load can be moved behind the wait for the others.
+    // The batch's first row offset for a lane is kept in one
+    // register (the empty asm stops the compiler from hoisting a lane
+    // offset per row out of the loop, which costs a register per row);
+    // each load adds a wave-uniform row offset.
+    auto stage_window = [&](const AngleEnt &e, float *yt) {
+        const int U0 = (int)(e.u01 & 0xffffu), Wc = (int)(e.u01 >> 16) - U0 + 1;
+        const int nrows = (int)(e.hn & 0xffffu), NT = (int)(e.hn >> 16);
         // staged rows; rows past V1 (only when the window is shorter than a
         // run) are zero
-        const int Hs = max(V1 - V0 + 1, NT);
-        const int VS1 = max(V1 - NT + 1, V0);
-
-        __syncthreads();   // previous angle's readers are done
-        // Columns on lanes, rows on waves (stride 4).  The loads of a batch
-        // of rows are issued before any of them is used, so their latencies
-        // overlap instead of adding up row after row.  They go through a
-        // buffer resource holding exactly rows V0 .. V1 of this projection:
-        // the range check returns zero for every row past V1 (the window's
-        // zero rows and a batch's rows past Hs) without touching memory, so
-        // no load needs a test of its own.  Byte offsets within the rows are
-        // 32-bit (nv nu < 2^24).  Every store is unconditional, so no load
-        // can be moved behind the wait for the others; one wave also writes
-        // the column table, its load issued with the rows' and stored after
-        // them, so that wave does not wait for it before issuing its row
-        // loads.  The batch's first row offset for a lane is kept in one
-        // register (the empty asm stops the compiler from hoisting a lane
-        // offset per row out of the loop, which costs a register per row);
-        // each load adds a wave-uniform row offset.
-        const float *proj = ws + ((size_t)a * g.nv + V0) * g.nu;   // row V0, ds-weighted
-        const __amdgpu_buffer_rsrc_t rows =
-            __builtin_amdgcn_make_buffer_rsrc((void *)proj, (short)0, (V1 - V0 + 1) * g.nu * 4,
-                                              kBufferWord3);
+        const int Hs = max(nrows, NT);
+        const float *proj = ws + ((size_t)e.a * g.nv + e.V0) * g.nu;   // row V0, ds-weighted
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)proj, (short)0, nrows * g.nu * 4, kBufferWord3);
         if constexpr (TALL) {
             // Batches no longer than the window needs: SB rows per wave
             // cover 4 SB rows, SB = 16 up to 64 rows, 20 up to 80, else 24
@@ -383,62 +453,47 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
             // further tenth of the staged rows but cost registers and were
             // slower.)
             if (Hs <= 64)
-                stage_tall<16>(g, a, rows, U0, Wc, Hs, HS, w, lane, yt, cr);
+                stage_tall<16>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else if (Hs <= 80)
-                stage_tall<20>(g, a, rows, U0, Wc, Hs, HS, w, lane, yt, cr);
+                stage_tall<20>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else
-                stage_tall<kSB>(g, a, rows, U0, Wc, Hs, HS, w, lane, yt, cr);
+                stage_tall<kSB>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+        } else if (Wc <= 32) {
+            if (Hs <= 32)
+                stage_short<4, true>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+            else if (Hs <= 64)
+                stage_short<8, true>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+            else
+                stage_short<12, true>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
         } else {
-            // Short columns: batches of kSB rows per wave whose rows past Hs
-            // (zeros) all go to row HS - 1, a spare row no tap reads (HS > H
-            // >= Hs).  Written out here rather than in a function like
-            // stage_tall, so these kernels compile as they did before the
-            // tall variant existed (the call changed their register
-            // allocation).
-            const int row_bytes = 4 * g.nu;
-            for (int uu = lane; uu < Wc; uu += 64) {
-                float4 ctab;
-                if (w == 0) {
-                    const ColRec col = g.cols[(size_t)a * g.nu + U0 + uu];
-                    ctab = make_float4(col.pb, col.ps, col.t0, col.tau);
-                }
-                const int cb = 4 * (U0 + uu);
-                float *dst = yt + (size_t)uu * HS;
-                for (int vv0 = w; vv0 < Hs; vv0 += 4 * kSB) {
-                    int off = cb + vv0 * row_bytes;
-                    asm volatile("" : "+v"(off));
-                    float val[kSB];
-#pragma unroll
-                    for (int jj = 0; jj < kSB; ++jj)
-                        val[jj] = __builtin_bit_cast(
-                            float, __builtin_amdgcn_raw_buffer_load_b32(
-                                       rows, off + 4 * jj * row_bytes, 0, 0));
-#pragma unroll
-                    for (int jj = 0; jj < kSB; ++jj)
-                        dst[min(vv0 + 4 * jj, HS - 1)] = val[jj];
-                }
-                if (w == 0)
-                    cr[uu] = ctab;
-            }
+            if (Hs <= 32)
+                stage_short<8, false>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+            else if (Hs <= 64)
+                stage_short<16, false>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+            else
+                stage_short<kSB, false>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
         }
-        __syncthreads();
+    };
 
-        // ---- this wave's KV voxel layers (z of the voxel centres +- one
+    // One angle's gather from its staged window.
+    auto gather = [&](const AngleEnt &e, uint2 range, const float *yt) {
+        const int U0 = (int)(e.u01 & 0xffffu), V0 = e.V0;
+        const int V1 = V0 + (int)(e.hn & 0xffffu) - 1, NT = (int)(e.hn >> 16);
+        const int VS1 = max(V1 - NT + 1, V0);
+        // this wave's KV voxel layers (z of the voxel centres +- one
         // pitch) land on rows [wv0, wv1] for every ray through the brick's
         // box (lambda is extreme at the box corners); a wave whose rows miss
         // the staged rows entirely has only zero weights and skips the angle
         // (wave-uniform branch; one row of margin for rounding).
-        {
-            const float zl = zc_w0 - g.vz, zh = zc_w0 + (float)(KV - 1) * g.vz + g.vz;
-            const float wv0 = fmaf(fminf(lmin * zl, lmax * zl) - g.off_v, inv_dv, g.cv);
-            const float wv1 = fmaf(fmaxf(lmin * zh, lmax * zh) - g.off_v, inv_dv, g.cv);
-            if (wv1 < (float)V0 - 1.0f || wv0 > (float)V1 + 1.0f)
-                continue;
-        }
-        // ---- gather with a compile-time tap count (NT rounded up to a
-        // supported count; extra taps read zero weight)
-        const GatherIn in{g, ar, yt, cr, HS, U0, U1, V0, VS1, k0, {pl0, pl1}, {sg0, sg1},
-                          inv_du, inv_rvs, A.rbias};
+        const float zl = zc_w0 - g.vz, zh = zc_w0 + (float)(KV - 1) * g.vz + g.vz;
+        const float wv0 = fmaf(fminf(e.lmin * zl, e.lmax * zl) - g.off_v, inv_dv, g.cv);
+        const float wv1 = fmaf(fmaxf(e.lmin * zh, e.lmax * zh) - g.off_v, inv_dv, g.cv);
+        if (wv1 < (float)V0 - 1.0f || wv0 > (float)V1 + 1.0f)
+            return;
+        // compile-time tap count (NT rounded up to a supported count; extra
+        // taps read zero weight)
+        const GatherIn in{g, e.x_lo, e.x_hi, yt, (const float4 *)(yt + A.W * HS), HS, U0, V0, VS1,
+                          k0, {pl[0], pl[1]}, {sg[0], sg[1]}, range, inv_rvs, A.rbias};
         switch (NT) {
         case 4: gather_angle<4, KV>(in, lo, hi); break;
         case 5: gather_angle<5, KV>(in, lo, hi); break;
@@ -458,6 +513,93 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
         case 24: gather_angle<24, KV>(in, lo, hi); break;
         case 28: gather_angle<28, KV>(in, lo, hi); break;
         default: gather_angle<32, KV>(in, lo, hi); break;
+        }
+    };
+
+    for (int base = 0; base < g.n_angles; base += kListAngles) {
+        __syncthreads();   // the readers of the previous list (or work item) are done
+        // ---- the next 32 angles at which the window meets the panel: columns
+        // and row taps from the table, rows from the extreme source-panel
+        // scales (positive) at the support's lowest and highest z
+        if (w == 0) {
+            AngleEnt e{};
+            bool seen = false;
+            e.a = base + lane;
+            if (lane < kListAngles && e.a < g.n_angles) {
+                const BrickWin bw = wcol[(size_t)e.a * wstep];
+                const AngRec ar = g.angs[e.a];
+                const int U0 = (int)(bw.u01 & 0xffffu);
+                const int U1 = min((int)(bw.u01 >> 16), U0 + A.W - 1);
+                const float vmin =
+                    fmaf(fminf(bw.lmin * zs0, bw.lmax * zs0) - g.off_v, inv_dv, g.cv);
+                const float vmax =
+                    fmaf(fmaxf(bw.lmin * zs1, bw.lmax * zs1) - g.off_v, inv_dv, g.cv);
+                const int V0 = max((int)floorf(vmin) - 2, 0);
+                const int V1 = min(min((int)ceilf(vmax) + 2, g.nv - 1), V0 + A.H - 1);
+                seen = U0 <= U1 && V0 <= V1;
+                e.u01 = (uint32_t)U0 | (uint32_t)U1 << 16;
+                e.V0 = V0;
+                e.hn = (uint32_t)(V1 - V0 + 1) | (uint32_t)bw.nt << 16;
+                e.x_lo = ar.x_lo;
+                e.x_hi = ar.x_hi;
+                e.lmin = bw.lmin;
+                e.lmax = bw.lmax;
+            }
+            const uint64_t m = __ballot(seen);
+            if (seen)
+                list[__builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)] = e;
+            if (lane == 0)
+                *listed = (int)__popcll(m);
+        }
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(*listed);
+        // ---- groups of four angles: wave w finds the column ranges of angle w
+        // of the group (all waves use them), from the records in that angle's
+        // window, or, where fewer than four windows fit, from a copy in the
+        // window's place before it is staged
+        for (int i0 = 0; i0 < n; i0 += kGroup) {
+            const int m = min(kGroup, n - i0);
+            const bool all = A.gw == kGroup;
+            if (i0 > 0)
+                __syncthreads();   // the previous group's readers are done
+            if (w < m) {
+                const AngleEnt e = uniform_ent(list[i0 + w]);
+                float4 *cr = (float4 *)(all ? lds + w * win + A.W * HS : lds + w * 4 * A.W);
+                stage_columns(g, e, lane, cr);
+                if (!all) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    ranges[w * 64 + lane] = column_ranges(g, e, pl, sg, inv_du, cr);
+                }
+            }
+            if (all) {
+                for (int i = 0; i < m; ++i)
+                    stage_window(uniform_ent(list[i0 + i]), lds + i * win);
+                if (w < m) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    ranges[w * 64 + lane] =
+                        column_ranges(g, uniform_ent(list[i0 + w]), pl, sg, inv_du,
+                                      (const float4 *)(lds + w * win + A.W * HS));
+                }
+            }
+            for (int i = 0; i < m; i += A.gw) {
+                const int mi = min(A.gw, m - i);
+                if (!all) {
+                    __syncthreads();   // the windows' readers, or the ranges', are done
+                    for (int j = 0; j < mi; ++j) {
+                        const AngleEnt e = uniform_ent(list[i0 + i + j]);
+                        float *yt = lds + j * win;
+                        stage_window(e, yt);
+                        if (w == j)
+                            stage_columns(g, e, lane, (float4 *)(yt + A.W * HS));
+                    }
+                }
+                __syncthreads();
+                for (int j = 0; j < mi; ++j)
+                    gather(uniform_ent(list[i0 + i + j]), ranges[(i + j) * 64 + lane],
+                           lds + j * win);
+            }
         }
     }
 
@@ -515,7 +657,7 @@ __host__ __device__ inline int slots_per_xcd(const BrickArgs &A)
 }
 
 template <class VS, int KV, bool TALL>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, 4)
 adjoint_brick(BrickArgs A, const float *__restrict__ ws, typename VS::T *__restrict__ vol)
 {
     extern __shared__ float lds[];
@@ -563,7 +705,7 @@ struct BatchAdjArgs {
 };
 
 template <class VS>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, 4)
 adjoint_batch(BatchAdjArgs B)
 {
     extern __shared__ float lds[];
@@ -587,21 +729,46 @@ adjoint_batch(BatchAdjArgs B)
 
 }  // namespace
 
+// Window columns, rounded up to even: with the column stride 2 mod 4 words
+// the column records behind a window are 16-byte aligned.
+static int even_width(const AdjPlan &p) { return p.W + (p.W & 1); }
+
+// Words of one panel window with its column records.
+static size_t window_words(const AdjPlan &p) { return (size_t)even_width(p) * (p.WS + 4); }
+
+// Four workgroups share a CU up to this many words each (40 KB, less the list
+// and ranges): with that many windows at a time a group of angles takes two
+// barriers and one round trip to memory instead of eight and four.
+static int windows_at_a_time(const AdjPlan &p)
+{
+    constexpr size_t kWords = 40 * 256 - (kGroup * 64 * 2 + kListAngles * 8 + 4);
+    return 4 * window_words(p) <= kWords ? 4 : 2 * window_words(p) <= kWords ? 2 : 1;
+}
+
+// Words the windows take; a group's column records use them too before fewer
+// than four windows are staged.
+static size_t window_area(const AdjPlan &p)
+{
+    const size_t n = windows_at_a_time(p), records = (size_t)kGroup * even_width(p) * 4;
+    return std::max(n * window_words(p), records);
+}
+
 static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p)
 {
     const int bk = 4 * p.KV;
-    return BrickArgs{g, p.wins, p.W, p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
+    return BrickArgs{g, p.wins, even_width(p), p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
                      (g.ny + kAdjBJ - 1) / kAdjBJ, (g.nz + bk - 1) / bk, p.KV,   // WS: column stride
-                     1.0f - adj_start_delta(g.nv)};
+                     windows_at_a_time(p), (int)window_area(p), 1.0f - adj_start_delta(g.nv)};
 }
 
-// The window and column table, or the final exchange (four shares per lane
-// and voxel layer, four waves) if that is larger.
+// The windows, the column ranges and the list of angles, or the final exchange
+// (four shares per lane and voxel layer, four waves) if that is larger.
 static size_t brick_lds(const AdjPlan &p)
 {
-    const size_t window = (size_t)p.W * p.WS + (size_t)p.W * 4;
+    const size_t gather = window_area(p) + kGroup * 64 * 2 +
+                          kListAngles * sizeof(AngleEnt) / sizeof(float) + 4;
     const size_t exchange = (size_t)4 * 4 * 64 * p.KV;
-    return std::max(window, exchange) * sizeof(float);
+    return std::max(gather, exchange) * sizeof(float);
 }
 
 static hipError_t launch_ds_weight(const DevGeom &g, const void *sino, cbct_dtype st, float *ws,
