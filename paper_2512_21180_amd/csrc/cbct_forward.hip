@@ -33,6 +33,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxR = 8;       // rays per thread
+constexpr int kFewR = 4;       // where there are few tiles (see the plan)
 // Planes whose boxes are loaded ahead (two: 7.83 ms against 7.82, 11 registers more).
 constexpr int kPlanes = 1;
 // Rays whose LDS reads run ahead of the arithmetic.  With all eight rays' reads
@@ -70,6 +71,7 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
                            const float *__restrict__ v, const float *__restrict__ vt,
                            typename SS::T *__restrict__ sino, float *lds)
 {
+    constexpr int NR = RC > 0 ? RC : kMaxR;
     const int R = RC > 0 ? RC : R_rt;
     const int tid = threadIdx.x;
     // the wave index is uniform: the staging's slot tests below are scalar
@@ -79,9 +81,9 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
     const int ul = min(uc, T.nu_t - 1);
     const ColRec c = g.cols[(size_t)T.a * g.nu + T.u0 + ul];
 
-    float kb[kMaxR], ks[kMaxR], acc[kMaxR];
+    float kb[NR], ks[NR], acc[NR];
 #pragma unroll
-    for (int r = 0; r < kMaxR; ++r) {
+    for (int r = 0; r < NR; ++r) {
         const int vr = T.v0 + min(row0 + min(r, R - 1), T.nv_t - 1);
         const float vz = g.rows[vr].x;
         kb[r] = fmaf(c.t0, vz, g.Kb);
@@ -201,7 +203,7 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
             (int)(lds_addr(buf) + 4u * (uint32_t)((int)qf - cb.qlo)) - cb.klo * (4 * kQS);
         // ray r's arithmetic runs while the reads of the next kAhead rays are
         // in flight; the scheduling barriers keep that order
-        float wk[kMaxR], v00[kMaxR], v10[kMaxR], v01[kMaxR], v11[kMaxR];
+        float wk[NR], v00[NR], v10[NR], v01[NR], v11[NR];
         auto read = [&](int r) {
             // z index k of the ray on this plane: its weight is the
             // exact fraction of k, its row address one floor conversion
@@ -220,9 +222,9 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
             if (r < R)
                 read(r);
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+        for (int r = 0; r < NR; ++r) {
             __builtin_amdgcn_sched_barrier(0);
-            if (r + kAhead < kMaxR && r + kAhead < R)
+            if (r + kAhead < NR && r + kAhead < R)
                 read(r + kAhead);
             __builtin_amdgcn_sched_barrier(0);
             if (r < R) {
@@ -259,17 +261,17 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
         // eight registers throughout)
         int rb = row0;
         asm volatile("" : "+v"(rb));
-        float ds[kMaxR];
+        float ds[NR];
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r)
+        for (int r = 0; r < NR; ++r)
             ds[r] = g.rows[T.v0 + min(rb + r, T.nv_t - 1)].y;
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+        for (int r = 0; r < NR; ++r) {
             ds[r] = ray_ds(c.dsf, c.n2, ds[r]);
             asm volatile("" : "+v"(ds[r]));
         }
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int vr = row0 + r;
             if (r < R && vr < T.nv_t)
                 SS::st(sino, ((size_t)T.a * g.nv + T.v0 + vr) * g.nu + T.u0 + uc, acc[r] * ds[r]);
@@ -346,6 +348,8 @@ forward_batch(BatchFwdArgs B)
     // (a uniform branch; the bits do not depend on the variant)
     if (C.R == kMaxR)
         sweep_tile<SS, kMaxR>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
+    else if (C.R == kFewR)
+        sweep_tile<SS, kFewR>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
     else
         sweep_tile<SS>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
 }
@@ -372,6 +376,8 @@ hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *
             auto *y = (typename SS::T *)sino;
             if (p.R == kMaxR)
                 hipLaunchKernelGGL((forward_sweep<SS, kMaxR>), grid, block, lds, s, A, v.vol, v.volt, y);
+            else if (p.R == kFewR)
+                hipLaunchKernelGGL((forward_sweep<SS, kFewR>), grid, block, lds, s, A, v.vol, v.volt, y);
             else
                 hipLaunchKernelGGL((forward_sweep<SS, 0>), grid, block, lds, s, A, v.vol, v.volt, y);
             return hipGetLastError();

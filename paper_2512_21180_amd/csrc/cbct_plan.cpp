@@ -244,6 +244,12 @@ AdjPlan adjoint_plan(const cbct_geom *g, const WinTable &t, int bk, int channels
 
 }  // namespace
 
+// Fewer tiles than this (four workgroups per CU) take half-height ones: a CU
+// then holds four or five small sweeps where it held two or three, which evens the
+// CUs out and hides the planes' latency (64^3, 64 projections of 128^2: 544
+// tiles 62.5 us, 1088 tiles 53.4 us).  The per-ray sums do not depend on it.
+constexpr size_t kFewTiles = 1024;
+
 void plan_host(cbct_geom *g)
 {
     const cbct_geom_desc &d = g->desc;
@@ -273,6 +279,11 @@ void plan_host(cbct_geom *g)
         }
         if (R > 0)
             break;
+    }
+    // few tiles of eight rays per thread: half-height ones
+    if (R == 8 && tb.tiles.size() < kFewTiles) {
+        R = 4;
+        tb = make_tiles(g, TU, (256 / TU) * R);
     }
     if (R > 0) {
         while (tb.tiles.size() % 8) {
