@@ -469,9 +469,11 @@ extern "C" cbct_status cbct_fdk(const cbct_geom *g, const float *sino, int windo
     A.hann = window;
     hipStream_t s = (hipStream_t)stream;
     const size_t rows = (size_t)n * d.nv;
-    if (d.nu <= kMmNu) {
-        // enough waves along the columns for whole rows, the others on more rows
-        const int wm = d.nu <= kMmN ? 4 : d.nu <= 2 * kMmN ? 2 : 1;
+    // enough waves along the columns for whole rows, the others on more rows;
+    // a few hundred rows make too few such workgroups (8 projections of 40 x 50:
+    // five, 21 us for the call against 17 us with one workgroup per row)
+    const int wm = d.nu <= kMmN ? 4 : d.nu <= 2 * kMmN ? 2 : 1;
+    if (d.nu <= kMmNu && rows >= (size_t)64 * 16 * wm) {
         const size_t lds =
             ((size_t)16 * wm * mm_stride(d.nu) + kMmN * (4 / wm) + ((d.nu + 3) & ~3)) *
             sizeof(float);
