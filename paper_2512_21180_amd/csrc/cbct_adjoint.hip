@@ -83,6 +83,8 @@ struct BrickArgs {
     float rbias;           // 1 - adj_start_delta(nv)
 };
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 __device__ inline float sat(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
 
 // A run's LDS address is a plain 32-bit number (lds_addr, lds_ptr): it comes
@@ -163,9 +165,11 @@ __device__ inline float centre_y(const DevGeom &g, float j)
 // voxels k0 + n.  NT taps per voxel and column (rows past the non-zero run
 // have zero weight).  Forced inline: a call would impose the calling
 // convention's register budget and stack on the kernel.
-template <int NT, int KV>
-__device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][KV],
-                                             float (&hi)[2][KV])
+// C channels share a run's columns, rows and weights; their values lie side by
+// side in the window.
+template <int NT, int KV, int C>
+__device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[C][2][KV],
+                                             float (&hi)[C][2][KV])
 {
     const DevGeom &g = in.g;
     const int HS = in.HS, U0 = in.U0, V0 = in.V0, VS1 = in.VS1;
@@ -206,7 +210,7 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][
             // (row 0 lies below the window when V0 > 0; every row read,
             // vsf >= V0, has a non-negative address); exact in FP32: LDS
             // addresses are far below 2^24
-            const float colb = (float)((int)lds_addr(yt) + 4 * ((u - U0) * HS - V0));
+            const float colb = (float)((int)lds_addr(yt) + 4 * C * ((u - U0) * HS - V0));
 #pragma unroll
             for (int n = 0; n < KV; ++n) {
                 // run start: the first row above v_c (floor(v_c) + 1), or one
@@ -218,19 +222,38 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[2][
                 // hat argument at the run start; (vsf - cv) is exact, which keeps
                 // the rounding of this difference of two large z indices small
                 float s = fmaf(t, fmaf(vsf - g.cv, g.rvs, g.rv0), KbK[n]);
-                const lds_float *py = lds_ptr((uint32_t)fmaf(vsf, 4.0f, colb));
-                float yv[NT];
-#pragma unroll
-                for (int m = 0; m < NT; ++m)
-                    yv[m] = py[m];
-                float csum = 0.0f;
+                const lds_float *py = lds_ptr((uint32_t)fmaf(vsf, 4.0f * C, colb));
+                float yv[NT][C];
 #pragma unroll
                 for (int m = 0; m < NT; ++m) {
-                    csum = fmaf(sat(1.0f - fabsf(s)), yv[m], csum);
+                    if constexpr (C == 4) {
+                        const f32x4 q = *(__attribute__((address_space(3))) const f32x4 *)(py + 4 * m);
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            yv[m][c] = q[c];
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < C; ++c)
+                            yv[m][c] = py[C * m + c];
+                    }
+                }
+                float csum[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    csum[c] = 0.0f;
+#pragma unroll
+                for (int m = 0; m < NT; ++m) {
+                    const float hat = sat(1.0f - fabsf(s));
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        csum[c] = fmaf(hat, yv[m][c], csum[c]);
                     s += beta;
                 }
-                lo[cls][n] = fmaf(wl, csum, lo[cls][n]);
-                hi[cls][n] = fmaf(f, csum, hi[cls][n]);
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    lo[c][cls][n] = fmaf(wl, csum[c], lo[c][cls][n]);
+                    hi[c][cls][n] = fmaf(f, csum[c], hi[c][cls][n]);
+                }
             }
         }
     }
@@ -307,27 +330,47 @@ __device__ inline void stage_columns(const DevGeom &g, const AngleEnt &e, int la
 // flight per lane.  Windows of up to 32 columns (HALF) put two rows on a
 // wave's lanes.  Rows past Hs (zeros) that would leave the column go to row
 // HS - 1, a spare row no tap reads (HS > H >= Hs).
-template <int SB, bool HALF>
+template <int SB, bool HALF, int C>
 __device__ __forceinline__ void stage_short(const DevGeom &g, __amdgpu_buffer_rsrc_t rows, int U0,
                                             int Wc, int Hs, int HS, int w, int lane, float *yt)
 {
     constexpr int kRows = HALF ? 8 : 4;   // rows of one load of the four waves
-    const int row_bytes = 4 * g.nu;
+    const int row_bytes = 4 * C * g.nu;
     const int r0 = HALF ? 2 * w + (lane >> 5) : w;
     for (int uu = HALF ? lane & 31 : lane; uu < Wc; uu += 64) {
-        float *dst = yt + (size_t)uu * HS;
+        float *dst = yt + (size_t)uu * HS * C;
         for (int v = 0; v < Hs; v += kRows * SB) {
-            int off = 4 * (U0 + uu) + (v + r0) * row_bytes;
+            int off = 4 * C * (U0 + uu) + (v + r0) * row_bytes;
             asm volatile("" : "+v"(off));   // one register (see gather_brick)
-            float val[SB];
+            float val[SB][C];
 #pragma unroll
-            for (int jj = 0; jj < SB; ++jj)
-                val[jj] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(
-                               rows, off + kRows * jj * row_bytes, 0, 0));
+            for (int jj = 0; jj < SB; ++jj) {
+                const int o = off + kRows * jj * row_bytes;
+                if constexpr (C == 4) {
+                    const auto d = __builtin_amdgcn_raw_buffer_load_b128(rows, o, 0, 0);
 #pragma unroll
-            for (int jj = 0; jj < SB; ++jj)
-                dst[min(v + r0 + kRows * jj, HS - 1)] = val[jj];
+                    for (int c = 0; c < 4; ++c)
+                        val[jj][c] = __uint_as_float(d[c]);
+                } else if constexpr (C == 2) {
+                    const auto d = __builtin_amdgcn_raw_buffer_load_b64(rows, o, 0, 0);
+                    val[jj][0] = __uint_as_float(d[0]);
+                    val[jj][1] = __uint_as_float(d[1]);
+                } else {
+                    val[jj][0] = __builtin_bit_cast(
+                        float, __builtin_amdgcn_raw_buffer_load_b32(rows, o, 0, 0));
+                }
+            }
+#pragma unroll
+            for (int jj = 0; jj < SB; ++jj) {
+                float *d = dst + (size_t)C * min(v + r0 + kRows * jj, HS - 1);
+                if constexpr (C == 4) {
+                    *(float4 *)d = make_float4(val[jj][0], val[jj][1], val[jj][2], val[jj][3]);
+                } else if constexpr (C == 2) {
+                    *(float2 *)d = make_float2(val[jj][0], val[jj][1]);
+                } else {
+                    *d = val[jj][0];
+                }
+            }
         }
     }
 }
@@ -378,14 +421,15 @@ __device__ __forceinline__ void stage_tall(const DevGeom &g, __amdgpu_buffer_rsr
 // the one below, on each axis) are added in a fixed order through LDS.
 // `lds` holds the panel window, column-major ([W][HS], HS = 2 mod 4, which
 // suits the gather's reads), and the column table; then the exchange.
-template <class VS, int KV, bool TALL>
+template <class VS, int KV, bool TALL, int C = 1>
 __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const float *ws,
-                                             typename VS::T *vol, float *lds)
+                                             typename VS::T *const (&vol)[C], float *lds)
 {
     constexpr int kBK = 4 * KV;
     constexpr int kSB = kStageRows;
     const DevGeom &g = A.g;
-    const int HS = A.HS, win = A.W * (HS + 4);          // words of one window and its columns
+    const int HS = A.HS, cols = A.W * HS * C;           // words before a window's column records
+    const int win = cols + 4 * A.W;                     // words of a window with them
     uint2 *ranges = (uint2 *)(lds + A.area);            // [kGroup][64]
     AngleEnt *list = (AngleEnt *)(ranges + kGroup * 64);
     int *listed = (int *)(list + kListAngles);
@@ -415,13 +459,13 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
     // z of this wave's first voxel layer (wave-uniform)
     const float zc_w0 = g.oz + ((float)k0 - 0.5f * (float)(g.nz - 1)) * g.vz;
     const float inv_rvs = 1.0f / g.rvs;
-    float lo[2][KV], hi[2][KV];
+    float lo[C][2][KV], hi[C][2][KV];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 2 * C; ++c)
 #pragma unroll
         for (int n = 0; n < KV; ++n) {
-            lo[c][n] = 0.0f;
-            hi[c][n] = 0.0f;
+            lo[c >> 1][c & 1][n] = 0.0f;
+            hi[c >> 1][c & 1][n] = 0.0f;
         }
 
     // One angle's window: rows V0 .. V1 of the ds-weighted projection through a
@@ -442,9 +486,9 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
         // staged rows; rows past V1 (only when the window is shorter than a
         // run) are zero
         const int Hs = max(nrows, NT);
-        const float *proj = ws + ((size_t)e.a * g.nv + e.V0) * g.nu;   // row V0, ds-weighted
+        const float *proj = ws + ((size_t)e.a * g.nv + e.V0) * g.nu * C;   // row V0, ds-weighted
         const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)proj, (short)0, nrows * g.nu * 4, kBufferWord3);
+            (void *)proj, (short)0, nrows * g.nu * 4 * C, kBufferWord3);
         if constexpr (TALL) {
             // Batches no longer than the window needs: SB rows per wave
             // cover 4 SB rows, SB = 16 up to 64 rows, 20 up to 80, else 24
@@ -458,20 +502,25 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
                 stage_tall<20>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else
                 stage_tall<kSB>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+        } else if constexpr (C > 1) {   // 16 registers of loads in flight
+            if (Wc <= 32)
+                stage_short<16 / C, true, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+            else
+                stage_short<16 / C, false, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
         } else if (Wc <= 32) {
             if (Hs <= 32)
-                stage_short<4, true>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+                stage_short<4, true, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else if (Hs <= 64)
-                stage_short<8, true>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+                stage_short<8, true, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else
-                stage_short<12, true>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+                stage_short<12, true, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
         } else {
             if (Hs <= 32)
-                stage_short<8, false>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+                stage_short<8, false, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else if (Hs <= 64)
-                stage_short<16, false>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+                stage_short<16, false, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
             else
-                stage_short<kSB, false>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
+                stage_short<kSB, false, C>(g, rows, U0, Wc, Hs, HS, w, lane, yt);
         }
     };
 
@@ -492,27 +541,37 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
             return;
         // compile-time tap count (NT rounded up to a supported count; extra
         // taps read zero weight)
-        const GatherIn in{g, e.x_lo, e.x_hi, yt, (const float4 *)(yt + A.W * HS), HS, U0, V0, VS1,
+        const GatherIn in{g, e.x_lo, e.x_hi, yt, (const float4 *)(yt + cols), HS, U0, V0, VS1,
                           k0, {pl[0], pl[1]}, {sg[0], sg[1]}, range, inv_rvs, A.rbias};
-        switch (NT) {
-        case 4: gather_angle<4, KV>(in, lo, hi); break;
-        case 5: gather_angle<5, KV>(in, lo, hi); break;
-        case 6: gather_angle<6, KV>(in, lo, hi); break;
-        case 7: gather_angle<7, KV>(in, lo, hi); break;
-        case 8: gather_angle<8, KV>(in, lo, hi); break;
-        case 9: gather_angle<9, KV>(in, lo, hi); break;
-        case 10: gather_angle<10, KV>(in, lo, hi); break;
-        case 11: gather_angle<11, KV>(in, lo, hi); break;
-        case 12: gather_angle<12, KV>(in, lo, hi); break;
-        case 13: gather_angle<13, KV>(in, lo, hi); break;
-        case 14: gather_angle<14, KV>(in, lo, hi); break;
-        case 15: gather_angle<15, KV>(in, lo, hi); break;
-        case 16: gather_angle<16, KV>(in, lo, hi); break;
-        case 18: gather_angle<18, KV>(in, lo, hi); break;
-        case 20: gather_angle<20, KV>(in, lo, hi); break;
-        case 24: gather_angle<24, KV>(in, lo, hi); break;
-        case 28: gather_angle<28, KV>(in, lo, hi); break;
-        default: gather_angle<32, KV>(in, lo, hi); break;
+        if constexpr (C > 1) {   // at most 8 (see kMaxTapsMc)
+            switch (NT) {
+            case 4: gather_angle<4, KV, C>(in, lo, hi); break;
+            case 5: gather_angle<5, KV, C>(in, lo, hi); break;
+            case 6: gather_angle<6, KV, C>(in, lo, hi); break;
+            case 7: gather_angle<7, KV, C>(in, lo, hi); break;
+            default: gather_angle<8, KV, C>(in, lo, hi); break;
+            }
+        } else {
+            switch (NT) {
+            case 4: gather_angle<4, KV, C>(in, lo, hi); break;
+            case 5: gather_angle<5, KV, C>(in, lo, hi); break;
+            case 6: gather_angle<6, KV, C>(in, lo, hi); break;
+            case 7: gather_angle<7, KV, C>(in, lo, hi); break;
+            case 8: gather_angle<8, KV, C>(in, lo, hi); break;
+            case 9: gather_angle<9, KV, C>(in, lo, hi); break;
+            case 10: gather_angle<10, KV, C>(in, lo, hi); break;
+            case 11: gather_angle<11, KV, C>(in, lo, hi); break;
+            case 12: gather_angle<12, KV, C>(in, lo, hi); break;
+            case 13: gather_angle<13, KV, C>(in, lo, hi); break;
+            case 14: gather_angle<14, KV, C>(in, lo, hi); break;
+            case 15: gather_angle<15, KV, C>(in, lo, hi); break;
+            case 16: gather_angle<16, KV, C>(in, lo, hi); break;
+            case 18: gather_angle<18, KV, C>(in, lo, hi); break;
+            case 20: gather_angle<20, KV, C>(in, lo, hi); break;
+            case 24: gather_angle<24, KV, C>(in, lo, hi); break;
+            case 28: gather_angle<28, KV, C>(in, lo, hi); break;
+            default: gather_angle<32, KV, C>(in, lo, hi); break;
+            }
         }
     };
 
@@ -564,7 +623,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
                 __syncthreads();   // the previous group's readers are done
             if (w < m) {
                 const AngleEnt e = uniform_ent(list[i0 + w]);
-                float4 *cr = (float4 *)(all ? lds + w * win + A.W * HS : lds + w * 4 * A.W);
+                float4 *cr = (float4 *)(all ? lds + w * win + cols : lds + w * 4 * A.W);
                 stage_columns(g, e, lane, cr);
                 if (!all) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -580,7 +639,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
                     __builtin_amdgcn_wave_barrier();
                     ranges[w * 64 + lane] =
                         column_ranges(g, uniform_ent(list[i0 + w]), pl, sg, inv_du,
-                                      (const float4 *)(lds + w * win + A.W * HS));
+                                      (const float4 *)(lds + w * win + cols));
                 }
             }
             for (int i = 0; i < m; i += A.gw) {
@@ -592,7 +651,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
                         float *yt = lds + j * win;
                         stage_window(e, yt);
                         if (w == j)
-                            stage_columns(g, e, lane, (float4 *)(yt + A.W * HS));
+                            stage_columns(g, e, lane, (float4 *)(yt + cols));
                     }
                 }
                 __syncthreads();
@@ -605,29 +664,32 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
 
     // ---- each output voxel's four shares, added in a fixed order: x planes
     // (lo of its own segment, hi of the segment below), then y planes (same)
-    __syncthreads();   // every wave is done with the window
     float *xch = lds + (size_t)w * (4 * 64 * KV);
-#pragma unroll
-    for (int n = 0; n < KV; ++n) {
-        xch[(0 * KV + n) * 64 + lane] = lo[0][n];
-        xch[(1 * KV + n) * 64 + lane] = hi[0][n];
-        xch[(2 * KV + n) * 64 + lane] = lo[1][n];
-        xch[(3 * KV + n) * 64 + lane] = hi[1][n];
-    }
-    __syncthreads();
     const int io = lane & 7, jo = lane >> 3;
     const int i = i0 + io, j = j0 + jo;
-    if (jo < kAdjBJ && i < g.nx && j < g.ny) {
-        const int xl = ((jo + 1) << 3) | io, xh = (jo << 3) | io;   // x-plane lanes
-        const int yl = jo * 9 + io + 1, yh = jo * 9 + io;           // y-plane lanes
+    const int xl = ((jo + 1) << 3) | io, xh = (jo << 3) | io;   // x-plane lanes
+    const int yl = jo * 9 + io + 1, yh = jo * 9 + io;           // y-plane lanes
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        __syncthreads();   // every wave is done with the window, or the last channel
 #pragma unroll
         for (int n = 0; n < KV; ++n) {
-            const int k = k0 + n;
-            if (k < g.nz) {
-                float v = xch[(0 * KV + n) * 64 + xl] + xch[(1 * KV + n) * 64 + xh];
-                v += xch[(2 * KV + n) * 64 + yl];
-                v += xch[(3 * KV + n) * 64 + yh];
-                VS::st(vol, ((size_t)k * g.ny + j) * g.nx + i, v);
+            xch[(0 * KV + n) * 64 + lane] = lo[c][0][n];
+            xch[(1 * KV + n) * 64 + lane] = hi[c][0][n];
+            xch[(2 * KV + n) * 64 + lane] = lo[c][1][n];
+            xch[(3 * KV + n) * 64 + lane] = hi[c][1][n];
+        }
+        __syncthreads();
+        if (jo < kAdjBJ && i < g.nx && j < g.ny) {
+#pragma unroll
+            for (int n = 0; n < KV; ++n) {
+                const int k = k0 + n;
+                if (k < g.nz) {
+                    float v = xch[(0 * KV + n) * 64 + xl] + xch[(1 * KV + n) * 64 + xh];
+                    v += xch[(2 * KV + n) * 64 + yl];
+                    v += xch[(3 * KV + n) * 64 + yh];
+                    VS::st(vol[c], ((size_t)k * g.ny + j) * g.nx + i, v);
+                }
             }
         }
     }
@@ -667,7 +729,65 @@ adjoint_brick(BrickArgs A, const float *__restrict__ ws, typename VS::T *__restr
     const int ch = blockIdx.y;
     const size_t nvox = (size_t)A.g.nx * A.g.ny * A.g.nz;
     const size_t nsino = (size_t)A.g.n_angles * A.g.nv * A.g.nu;
-    gather_brick<VS, KV, TALL>(A, b, ws + ch * nsino, vol + ch * nvox, lds);
+    typename VS::T *const out[1] = {vol + ch * nvox};
+    gather_brick<VS, KV, TALL>(A, b, ws + ch * nsino, out, lds);
+}
+
+// ---- C channels of one geometry in one gather --------------------------------
+
+// A run's rows, their weights and the columns' set-up are the same for every
+// channel: per run of NT taps C channels take 8 + NT (2 + C) + 2 C vector
+// instructions instead of C (10 + 3 NT), and a brick's ranges and lists are made once.
+// For windows that hold C channels in a workgroup's share of the LDS and runs
+// of at most 8 taps.  Four channels take bricks of at most eight layers, whose
+// sums and taps fit the 168 registers of three waves per SIMD.  Four channels of
+// 128^3 x 180 x 256^2, projection and gradient together: 6.50 ms channel by channel, 5.30 so;
+// 5.78 as two pairs, 5.89 with sixteen layers (65 registers spilled).
+constexpr int kMaxTapsMc = 8;
+
+template <int C>
+struct McAdjArgs {
+    BrickArgs A;
+    const float *ws;       // [n_angles][nv][nu][C], ds-weighted
+    float *vol[C];
+};
+
+template <int KV, int C>
+__global__ void __launch_bounds__(kThreads, 3)
+adjoint_mc(McAdjArgs<C> B)
+{
+    extern __shared__ float lds[];
+    const int b = brick_of_slot(B.A, blockIdx.x & 7, blockIdx.x >> 3);
+    if (b < 0)
+        return;
+    gather_brick<F32, KV, false, C>(B.A, b, B.ws, B.vol, lds);
+}
+
+struct McSinos {
+    const float *y[4];
+};
+
+// ds_weight for C channels, packed.
+template <int C>
+__global__ void __launch_bounds__(kThreads)
+ds_weight_mc(DevGeom g, McSinos y, float *__restrict__ out)
+{
+    const int row = blockIdx.x;   // a * nv + v
+    const int a = row / g.nv, v = row - a * g.nv;
+    const size_t base = (size_t)row * g.nu;
+    const float v2 = g.rows[v].y;
+    const ColRec *cols = g.cols + (size_t)a * g.nu;
+    for (int u = threadIdx.x; u < g.nu; u += kThreads) {
+        const ColRec c = cols[u];
+        const float ds = ray_ds(c.dsf, c.n2, v2);
+        if constexpr (C == 4)
+            *(float4 *)(out + 4 * (base + u)) =
+                make_float4(y.y[0][base + u] * ds, y.y[1][base + u] * ds, y.y[2][base + u] * ds,
+                            y.y[3][base + u] * ds);
+        else
+            *(float2 *)(out + 2 * (base + u)) =
+                make_float2(y.y[0][base + u] * ds, y.y[1][base + u] * ds);
+    }
 }
 
 // The ds-weighted copy of a sinogram that the bricks stage from:
@@ -719,7 +839,7 @@ adjoint_batch(BatchAdjArgs B)
     const int b = brick_of_slot(C.A, xc, li - B.first[cs]);
     if (b < 0)
         return;
-    auto *vs = (typename VS::T *)C.vol;
+    typename VS::T *const vs[1] = {(typename VS::T *)C.vol};
     switch (C.A.KV) {   // uniform over the workgroup
     case 4: gather_brick<VS, 4, false>(C.A, b, C.ws, vs, lds); break;
     case 2: gather_brick<VS, 2, false>(C.A, b, C.ws, vs, lds); break;
@@ -733,39 +853,44 @@ adjoint_batch(BatchAdjArgs B)
 // the column records behind a window are 16-byte aligned.
 static int even_width(const AdjPlan &p) { return p.W + (p.W & 1); }
 
-// Words of one panel window with its column records.
-static size_t window_words(const AdjPlan &p) { return (size_t)even_width(p) * (p.WS + 4); }
+// Words of one panel window of C channels with its column records.
+static size_t window_words(const AdjPlan &p, int C)
+{
+    return (size_t)even_width(p) * ((size_t)p.WS * C + 4);
+}
 
 // Four workgroups share a CU up to this many words each (40 KB, less the list
 // and ranges): with that many windows at a time a group of angles takes two
 // barriers and one round trip to memory instead of eight and four.
-static int windows_at_a_time(const AdjPlan &p)
+constexpr size_t kShareWords = 40 * 256 - (kGroup * 64 * 2 + kListAngles * 8 + 4);
+
+static int windows_at_a_time(const AdjPlan &p, int C)
 {
-    constexpr size_t kWords = 40 * 256 - (kGroup * 64 * 2 + kListAngles * 8 + 4);
-    return 4 * window_words(p) <= kWords ? 4 : 2 * window_words(p) <= kWords ? 2 : 1;
+    const size_t w = window_words(p, C);
+    return 4 * w <= kShareWords ? 4 : 2 * w <= kShareWords ? 2 : 1;
 }
 
 // Words the windows take; a group's column records use them too before fewer
 // than four windows are staged.
-static size_t window_area(const AdjPlan &p)
+static size_t window_area(const AdjPlan &p, int C)
 {
-    const size_t n = windows_at_a_time(p), records = (size_t)kGroup * even_width(p) * 4;
-    return std::max(n * window_words(p), records);
+    const size_t n = windows_at_a_time(p, C), records = (size_t)kGroup * even_width(p) * 4;
+    return std::max(n * window_words(p, C), records);
 }
 
-static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p)
+static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p, int C = 1)
 {
     const int bk = 4 * p.KV;
     return BrickArgs{g, p.wins, even_width(p), p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
                      (g.ny + kAdjBJ - 1) / kAdjBJ, (g.nz + bk - 1) / bk, p.KV,   // WS: column stride
-                     windows_at_a_time(p), (int)window_area(p), 1.0f - adj_start_delta(g.nv)};
+                     windows_at_a_time(p, C), (int)window_area(p, C), 1.0f - adj_start_delta(g.nv)};
 }
 
 // The windows, the column ranges and the list of angles, or the final exchange
 // (four shares per lane and voxel layer, four waves) if that is larger.
-static size_t brick_lds(const AdjPlan &p)
+static size_t brick_lds(const AdjPlan &p, int C = 1)
 {
-    const size_t gather = window_area(p) + kGroup * 64 * 2 +
+    const size_t gather = window_area(p, C) + kGroup * 64 * 2 +
                           kListAngles * sizeof(AngleEnt) / sizeof(float) + 4;
     const size_t exchange = (size_t)4 * 4 * 64 * p.KV;
     return std::max(gather, exchange) * sizeof(float);
@@ -781,6 +906,67 @@ static hipError_t launch_ds_weight(const DevGeom &g, const void *sino, cbct_dtyp
         hipLaunchKernelGGL((ds_weight<SS>), grid, block, 0, s, g, (const typename SS::T *)sino, ws);
         return hipGetLastError();
     });
+}
+
+// Bricks from which channels are gathered together: four workgroups per CU are
+// left (with fewer, the channels' bricks side by side fill the chip better).
+constexpr long kMcBricks = 1024;
+
+int adjoint_mc_channels(const cbct_geom *g, int left)
+{
+    const AdjPlan &p = g->adj;
+    if (!p.ok || p.NTmax > kMaxTapsMc)
+        return 1;
+    const BrickArgs A = brick_args(g->dev, p);
+    if ((long)A.nbx * A.nby * A.nbz < kMcBricks)
+        return 1;
+    for (int c : {4, 2})
+        if (left >= c && window_words(p, c) <= kShareWords)
+            return c;
+    return 1;
+}
+
+template <int C>
+static hipError_t launch_mc(const cbct_geom *g, const float *const *sinos, float *const *vols,
+                            float *ws, hipStream_t s)
+{
+    const DevGeom &d = g->dev;
+    AdjPlan p = g->adj;
+    if (C == 4)
+        p.KV = std::min(p.KV, 2);   // the plan's window holds the shorter bricks' too
+    McAdjArgs<C> B{brick_args(d, p, C), ws, {}};
+    McSinos y{};
+    for (int c = 0; c < C; ++c) {
+        B.vol[c] = vols[c];
+        y.y[c] = sinos[c];
+    }
+    const size_t lds = brick_lds(p, C);
+    const dim3 grid(8 * slots_per_xcd(B.A)), block(kThreads);
+    hipLaunchKernelGGL(ds_weight_mc<C>, dim3((unsigned)(d.n_angles * d.nv)), block, 0, s, d, y, ws);
+    if constexpr (C == 2) {
+        if (p.KV == 4) {
+            hipLaunchKernelGGL((adjoint_mc<4, 2>), grid, block, lds, s, B);
+            return hipGetLastError();
+        }
+    }
+    if (p.KV == 2)
+        hipLaunchKernelGGL((adjoint_mc<2, C>), grid, block, lds, s, B);
+    else
+        hipLaunchKernelGGL((adjoint_mc<1, C>), grid, block, lds, s, B);
+    return hipGetLastError();
+}
+
+hipError_t launch_adjoint_mc(const cbct_geom *g, int C, const float *const *sinos,
+                             float *const *vols, hipStream_t s)
+{
+    const size_t nsino = (size_t)g->dev.n_angles * g->dev.nv * g->dev.nu;
+    ScratchLease lease;
+    hipError_t e = scratch_acquire(nsino * C * sizeof(float), s, lease);
+    if (e == hipSuccess)
+        e = C == 4 ? launch_mc<4>(g, sinos, vols, (float *)lease.ptr, s)
+                   : launch_mc<2>(g, sinos, vols, (float *)lease.ptr, s);
+    const hipError_t r = scratch_release(s, lease);
+    return e != hipSuccess ? e : r;
 }
 
 hipError_t launch_adjoint_brick(const DevGeom &g, const AdjPlan &p, const void *sino,

@@ -55,8 +55,31 @@ hipError_t launch_forward(const cbct_geom *g, const void *vol, cbct_dtype vt, vo
 hipError_t launch_adjoint(const cbct_geom *g, const void *sino, cbct_dtype st, void *vol,
                           cbct_dtype vt, int channels, hipStream_t s)
 {
-    if (g->adj.ok)
-        return launch_adjoint_brick(g->dev, g->adj, sino, st, vol, vt, channels, s);
+    if (g->adj.ok) {
+        // FP32 channels go through the multichannel gather in fours and twos
+        // where it takes them (same bits), the rest in one launch
+        int c0 = 0;
+        if (st == CBCT_F32 && vt == CBCT_F32) {
+            const size_t nvox = (size_t)g->desc.nx * g->desc.ny * g->desc.nz;
+            const size_t nsino = (size_t)g->desc.n_angles * g->desc.nv * g->desc.nu;
+            for (int c; (c = adjoint_mc_channels(g, channels - c0)) > 1; c0 += c) {
+                const float *ys[kMaxMcChannels];
+                float *xs[kMaxMcChannels];
+                for (int t = 0; t < c; ++t) {
+                    ys[t] = (const float *)sino + (c0 + t) * nsino;
+                    xs[t] = (float *)vol + (c0 + t) * nvox;
+                }
+                const hipError_t e = launch_adjoint_mc(g, c, ys, xs, s);
+                if (e != hipSuccess)
+                    return e;
+            }
+            if (c0 == channels)
+                return hipSuccess;
+            sino = (const float *)sino + c0 * nsino;
+            vol = (float *)vol + c0 * nvox;
+        }
+        return launch_adjoint_brick(g->dev, g->adj, sino, st, vol, vt, channels - c0, s);
+    }
     return launch_adjoint_simple(g->dev, sino, st, vol, vt, channels, s);
 }
 
@@ -180,6 +203,36 @@ static hipError_t batch_forward_groups(int n, const cbct_geom *const *g,
     return hipSuccess;
 }
 
+// The same for the adjoint: chunks of the channels its gather takes together,
+// a launch each.
+static hipError_t batch_adjoint_groups(int n, const cbct_geom *const *g, const void *const *sinos,
+                                       void *const *vols, std::vector<char> &done, hipStream_t s)
+{
+    std::vector<int> idx;
+    for (int i = 0; i < n; ++i) {
+        if (done[i])
+            continue;
+        idx.clear();
+        for (int j = i; j < n; ++j)
+            if (!done[j] && g[j] == g[i])
+                idx.push_back(j);
+        size_t k = 0;
+        for (int c; (c = adjoint_mc_channels(g[i], (int)(idx.size() - k))) > 1; k += c) {
+            const float *ys[kMaxMcChannels];
+            float *xs[kMaxMcChannels];
+            for (int t = 0; t < c; ++t) {
+                ys[t] = (const float *)sinos[idx[k + t]];
+                xs[t] = (float *)vols[idx[k + t]];
+                done[idx[k + t]] = 1;
+            }
+            const hipError_t e = launch_adjoint_mc(g[i], c, ys, xs, s);
+            if (e != hipSuccess)
+                return e;
+        }
+    }
+    return hipSuccess;
+}
+
 static cbct_status check_batch(int n, const cbct_geom *const *g, const void *const *a,
                                const void *const *b, cbct_dtype t1, cbct_dtype t2)
 {
@@ -254,6 +307,14 @@ extern "C" cbct_status cbct_batch_adjoint(int n, const cbct_geom *const *g, cons
     if (s != CBCT_OK)
         return s;
     hipStream_t hs = (hipStream_t)stream;
+    // FP32 cases that share a geometry handle run through the multichannel
+    // gather where it takes them (same bits), the rest as below
+    std::vector<char> done(n, 0);
+    if (vt == CBCT_F32 && st == CBCT_F32) {
+        hipError_t e = batch_adjoint_groups(n, g, sinos, vols, done, hs);
+        if (e != hipSuccess)
+            return finish(e);
+    }
     const cbct_geom *gg[kMaxBatch];
     const void *yy[kMaxBatch];
     void *xx[kMaxBatch];
@@ -265,6 +326,8 @@ extern "C" cbct_status cbct_batch_adjoint(int n, const cbct_geom *const *g, cons
     };
     for (int i = 0; i < n; ++i) {
         hipError_t e = hipSuccess;
+        if (done[i])
+            continue;
         if (!g[i]->adj.ok) {
             e = launch_adjoint(g[i], sinos[i], st, vols[i], vt, 1, hs);
         } else {

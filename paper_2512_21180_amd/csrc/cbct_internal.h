@@ -240,6 +240,16 @@ int forward_mc_max_channels(const cbct_geom *g);
 hipError_t launch_forward_mc(int n, const cbct_geom *const *g, const float *const *vols,
                              float *const *sinos, int C, hipStream_t s);
 
+// Multichannel adjoint (cbct_adjoint.hip): C = 2 or 4 FP32 channels of one
+// geometry in one gather, the same sums as single-channel calls (a brick of
+// another height may clamp a run at its window's edge by a row of weight at
+// rounding level).
+// adjoint_mc_channels: how many of `left` channels the next gather takes
+// together (1: none, the single-channel kernels).
+int adjoint_mc_channels(const cbct_geom *g, int left);
+hipError_t launch_adjoint_mc(const cbct_geom *g, int C, const float *const *sinos,
+                             float *const *vols, hipStream_t s);
+
 // Dispatch to the tiled kernels when the plan allows, else the simple ones.
 hipError_t launch_forward(const cbct_geom *g, const void *vol, cbct_dtype vt, void *sino,
                           cbct_dtype st, int channels, hipStream_t s);
