@@ -4,7 +4,7 @@
 // latent.
 //
 // Forward / data gradient (conv3): implicit GEMM per wavefront: M = 16
-// consecutive x positions of one (z, y) row, N = 16 output channels,
+// output channels, N = 16 consecutive x positions of one (z, y) row,
 // K = 27 taps x 16 input channels, two taps per v_mfma_f32_16x16x32_bf16
 // (14 MFMAs per tile).  Lane l supplies, for MFMA p, 8 input channels
 // (8 (l/16) % 16 ..) of tap 2p + l/32 at position x0 + l%16: one 16-byte
@@ -43,6 +43,14 @@ __device__ inline uint16_t f2bf(float v)
     if ((b & 0x7f800000u) == 0x7f800000u && (b & 0x007fffffu))
         return (uint16_t)((b >> 16) | 0x0040u);
     return (uint16_t)((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
+}
+
+// Two values rounded to nearest even, the first in the low half.
+__device__ inline uint32_t pk_bf(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf2));
 }
 
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
@@ -160,12 +168,12 @@ k_conv3(ConvArgs A)
         }
     };
 
-    const int m = lane & 15;          // position within the tile (A rows) / output channel (B cols)
+    const int m = lane & 15;          // output channel (A rows) / position within the tile (B cols)
     const int kb = lane >> 4;         // k block: tap 2p + (kb >> 1), channels 8 (kb & 1) ..
     const int hh = kb & 1;
 
     // weights: staged once in LDS (27 x 16 x 16 bf16, coalesced), then
-    // B[k][n] for n = m (output channel), 8 input channels of half hh, into
+    // A[n][k] for n = m (output channel), 8 input channels of half hh, into
     // registers (the data gradient's transposed kernel gathered from LDS)
     {
         uint4 *wl = &halo[0][0][0];
@@ -203,8 +211,11 @@ k_conv3(ConvArgs A)
         }
     }
     __syncthreads();   // weights read before the halo overwrites them
-    const int co = m;
-    const float b = A.bias ? A.bias[co] : 0.0f;
+    const int c0 = 4 * kb;            // this lane's output channels in the epilogue: c0 .. c0 + 3
+    float b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        b[i] = A.bias ? A.bias[c0 + i] : 0.0f;
     const int y = y0 + w;
     const bool row_live = y < A.ny;   // uniform per wave
     const int ntx = min(kBX / 16, (A.nx - x0 + 15) / 16);   // live tiles (uniform)
@@ -222,16 +233,15 @@ k_conv3(ConvArgs A)
         const bool more = z + 1 < z1;   // uniform: the next plane needs z + 2
         // the epilogue's mask values, loaded ahead of the halo prefetch so
         // that waiting for them does not wait for it
-        uint16_t mk[kBX / 16][4];
+        uint2 mk[kBX / 16];
         if (MASK && row_live) {
 #pragma unroll
-            for (int tx = 0; tx < kBX / 16; ++tx)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int xo = x0 + 16 * tx + 4 * kb + i;
-                    mk[tx][i] = xo < A.nx
-                        ? A.mask[(((size_t)z * A.ny + y) * A.nx + xo) * 16 + co] : (uint16_t)0;
-                }
+            for (int tx = 0; tx < kBX / 16; ++tx) {
+                const int xo = x0 + 16 * tx + m;
+                mk[tx] = xo < A.nx ? *reinterpret_cast<const uint2 *>(
+                                         A.mask + (((size_t)z * A.ny + y) * A.nx + xo) * 16 + c0)
+                                   : make_uint2(0u, 0u);
+            }
         }
         if (more)
             load_plane(z + 2, pre);      // in flight during this plane's MFMAs
@@ -266,34 +276,41 @@ k_conv3(ConvArgs A)
                         if (t < 27)
                             a = __builtin_bit_cast(
                                 bf16x8, (&halo[0][0][0])[(MASK ? base(p) : bases[MASK ? 0 : p]) + 16 * tx]);
-                        acc[tx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, wr[p], acc[tx], 0, 0, 0);
+                        acc[tx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[p], a, acc[tx], 0, 0, 0);
                     }
                 }
             }
-            // epilogue: lane holds rows 4 kb + i (positions), column m (output channel)
+            // epilogue: lane holds rows c0 + i (output channels), column m
+            // (position): the four channels of a position are one 8-byte
+            // word of the channel-last arrays, a tile 512 bytes in a row
 #pragma unroll
             for (int tx = 0; tx < kBX / 16; ++tx) {
                 if (tx >= ntx)
                     break;
+                const int xo = x0 + 16 * tx + m;
+                if (xo >= A.nx)
+                    continue;
+                const size_t pos = ((size_t)z * A.ny + y) * A.nx + xo;
+                float v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int xo = x0 + 16 * tx + 4 * kb + i;
-                    if (xo >= A.nx)
-                        continue;
-                    const size_t pos = ((size_t)z * A.ny + y) * A.nx + xo;
-                    float v = acc[tx][i] + b;
+                    v[i] = acc[tx][i] + b[i];
                     if (MASK) {
-                        const uint16_t hm = mk[tx][i];
+                        const uint32_t hm = (i < 2 ? mk[tx].x : mk[tx].y) >> (16 * (i & 1));
                         const bool positive = !(hm & 0x8000u) && (hm & 0x7fffu);
-                        v = positive ? v : A.slope * v;
+                        v[i] = positive ? v[i] : A.slope * v[i];
                     }
                     if (A.act)
-                        v = v > 0.0f ? v : A.slope * v;
-                    if (A.y_cl)
-                        A.y_cl[pos * 16 + co] = f2bf(v);
-                    if (co < A.n_cf) {
-                        float *dst = A.y_cf.p[co] + pos;
-                        *dst = A.accumulate ? fmaf(A.alpha, v, *dst) : v;
+                        v[i] = v[i] > 0.0f ? v[i] : A.slope * v[i];
+                }
+                if (A.y_cl)
+                    *reinterpret_cast<uint2 *>(A.y_cl + pos * 16 + c0) =
+                        make_uint2(pk_bf(v[0], v[1]), pk_bf(v[2], v[3]));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (c0 + i < A.n_cf) {
+                        float *dst = A.y_cf.p[c0 + i] + pos;
+                        *dst = A.accumulate ? fmaf(A.alpha, v[i], *dst) : v[i];
                     }
                 }
             }
