@@ -700,22 +700,36 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
 // XCD holds an even share of cheap and costly bricks), in the order bx, bz,
 // row: workgroups resident together on one XCD are neighbouring bricks whose
 // panel windows overlap in its L2 (adjoint 33 -> 27 ms for the clinical
-// case; a contiguous brick range per XCD unbalances the XCDs, 71 ms).
+// case at the time; a contiguous brick range per XCD unbalances the XCDs, 71 ms).
+// Rows past the last multiple of eight are dealt out by brick columns, so no
+// XCD has a row more than another: with whole rows 10 rows (64^3) gave two XCDs
+// twice the others' work, 19 rows (128^3) three XCDs half as much again.
 // Slot li of XCD xc -> brick index, or -1 for the padding slots.
 __device__ inline int brick_of_slot(const BrickArgs &A, int xc, int li)
 {
-    const int plane = A.nbx * A.nbz;
-    const int by = xc + 8 * (li / plane);
-    if (by >= A.nby)
-        return -1;
-    const int bz = (li % plane) / A.nbx, bx = li % A.nbx;
+    const int plane = A.nbx * A.nbz, turns = A.nby / 8;
+    int bx, by, bz;
+    if (li < plane * turns) {
+        by = xc + 8 * (li / plane);
+        bz = (li % plane) / A.nbx;
+        bx = li % A.nbx;
+    } else {
+        const int columns = (A.nby % 8) * A.nbx, each = (columns + 7) / 8;
+        li -= plane * turns;
+        const int c = xc + 8 * (li % each);
+        if (c >= columns)
+            return -1;
+        by = 8 * turns + c / A.nbx;
+        bx = c % A.nbx;
+        bz = li / each;
+    }
     return (bz * A.nby + by) * A.nbx + bx;
 }
 
 // Slots per XCD of one case (padded so that every XCD has the same count).
 __host__ __device__ inline int slots_per_xcd(const BrickArgs &A)
 {
-    return A.nbx * A.nbz * ((A.nby + 7) / 8);
+    return A.nbz * (A.nbx * (A.nby / 8) + ((A.nby % 8) * A.nbx + 7) / 8);
 }
 
 template <class VS, int KV, bool TALL>
