@@ -80,6 +80,7 @@ struct BrickArgs {
     int KV;                // voxels per lane along z (bricks 8 x 7 x 4 KV)
     int gw;                // panel windows staged at a time: 4, 2 or 1
     int area;              // LDS words of the windows
+    int split;             // ranges of angles gathered apart
     float rbias;           // 1 - adj_start_delta(nv)
 };
 
@@ -419,11 +420,14 @@ __device__ __forceinline__ void stage_tall(const DevGeom &g, __amdgpu_buffer_rsr
 // (nine segments serve the eight output columns).  After the last angle the
 // four shares each output voxel receives (lo of its own segment and hi of
 // the one below, on each axis) are added in a fixed order through LDS.
+// Only the given range of the angles is gathered; where there are several,
+// `part` receives its sums in FP32.
 // `lds` holds the panel window, column-major ([W][HS], HS = 2 mod 4, which
 // suits the gather's reads), and the column table; then the exchange.
 template <class VS, int KV, bool TALL, int C = 1>
-__device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const float *ws,
-                                             typename VS::T *const (&vol)[C], float *lds)
+__device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int range,
+                                             const float *ws, typename VS::T *const (&vol)[C],
+                                             float *part, float *lds)
 {
     constexpr int kBK = 4 * KV;
     constexpr int kSB = kStageRows;
@@ -434,6 +438,9 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
     AngleEnt *list = (AngleEnt *)(ranges + kGroup * 64);
     int *listed = (int *)(list + kListAngles);
 
+    // this range of the angles
+    const int per = (g.n_angles + A.split - 1) / A.split;
+    const int a_lo = range * per, a_hi = min(a_lo + per, g.n_angles);
     const int bx = b % A.nbx, by = (b / A.nbx) % A.nby, bz = b / (A.nbx * A.nby);
 
     // the wave index is uniform (scalar registers for its row and layer indices)
@@ -575,7 +582,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
         }
     };
 
-    for (int base = 0; base < g.n_angles; base += kListAngles) {
+    for (int base = a_lo; base < a_hi; base += kListAngles) {
         __syncthreads();   // the readers of the previous list (or work item) are done
         // ---- the next 32 angles at which the window meets the panel: columns
         // and row taps from the table, rows from the extreme source-panel
@@ -584,7 +591,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
             AngleEnt e{};
             bool seen = false;
             e.a = base + lane;
-            if (lane < kListAngles && e.a < g.n_angles) {
+            if (lane < kListAngles && e.a < a_hi) {
                 const BrickWin bw = wcol[(size_t)e.a * wstep];
                 const AngRec ar = g.angs[e.a];
                 const int U0 = (int)(bw.u01 & 0xffffu);
@@ -688,7 +695,11 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, const fl
                     float v = xch[(0 * KV + n) * 64 + xl] + xch[(1 * KV + n) * 64 + xh];
                     v += xch[(2 * KV + n) * 64 + yl];
                     v += xch[(3 * KV + n) * 64 + yh];
-                    VS::st(vol[c], ((size_t)k * g.ny + j) * g.nx + i, v);
+                    const size_t at = ((size_t)k * g.ny + j) * g.nx + i;
+                    if (C == 1 && part)
+                        part[at] = v;
+                    else
+                        VS::st(vol[c], at, v);
                 }
             }
         }
@@ -734,7 +745,8 @@ __host__ __device__ inline int slots_per_xcd(const BrickArgs &A)
 
 template <class VS, int KV, bool TALL>
 __global__ void __launch_bounds__(kThreads, 4)
-adjoint_brick(BrickArgs A, const float *__restrict__ ws, typename VS::T *__restrict__ vol)
+adjoint_brick(BrickArgs A, const float *__restrict__ ws, typename VS::T *__restrict__ vol,
+              float *__restrict__ part)
 {
     extern __shared__ float lds[];
     const int b = brick_of_slot(A, blockIdx.x & 7, blockIdx.x >> 3);
@@ -744,7 +756,23 @@ adjoint_brick(BrickArgs A, const float *__restrict__ ws, typename VS::T *__restr
     const size_t nvox = (size_t)A.g.nx * A.g.ny * A.g.nz;
     const size_t nsino = (size_t)A.g.n_angles * A.g.nv * A.g.nu;
     typename VS::T *const out[1] = {vol + ch * nvox};
-    gather_brick<VS, KV, TALL>(A, b, ws + ch * nsino, out, lds);
+    const size_t at = ((size_t)blockIdx.z * gridDim.y + ch) * nvox;
+    gather_brick<VS, KV, TALL>(A, b, blockIdx.z, ws + ch * nsino, out, part ? part + at : nullptr,
+                               lds);
+}
+
+// The ranges' volumes added in order.
+template <class VS>
+__global__ void __launch_bounds__(kThreads)
+add_ranges(size_t n, int split, const float *__restrict__ part, typename VS::T *__restrict__ vol)
+{
+    const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n)
+        return;
+    float v = part[i];
+    for (int r = 1; r < split; ++r)
+        v += part[r * n + i];
+    VS::st(vol, i, v);
 }
 
 // ---- C channels of one geometry in one gather --------------------------------
@@ -774,7 +802,7 @@ adjoint_mc(McAdjArgs<C> B)
     const int b = brick_of_slot(B.A, blockIdx.x & 7, blockIdx.x >> 3);
     if (b < 0)
         return;
-    gather_brick<F32, KV, false, C>(B.A, b, B.ws, B.vol, lds);
+    gather_brick<F32, KV, false, C>(B.A, b, 0, B.ws, B.vol, nullptr, lds);
 }
 
 struct McSinos {
@@ -830,11 +858,12 @@ struct AdjCase {
     BrickArgs A;
     const float *ws;   // the case's ds-weighted sinogram
     void *vol;
+    float *part;       // partial volumes of the ranges of angles, if several
 };
 
 struct BatchAdjArgs {
     int n_cases, n_items;
-    int first[kMaxBatch + 1];   // first slot (per XCD) of each case
+    int first[kMaxBatch + 1];   // first slot (per XCD) of each case, its ranges in turn
     AdjCase c[kMaxBatch];
 };
 
@@ -850,14 +879,17 @@ adjoint_batch(BatchAdjArgs B)
     while (cs + 1 < B.n_cases && li >= B.first[cs + 1])
         ++cs;
     const AdjCase &C = B.c[cs];
-    const int b = brick_of_slot(C.A, xc, li - B.first[cs]);
+    const int slots = slots_per_xcd(C.A), range = (li - B.first[cs]) / slots;
+    const int b = brick_of_slot(C.A, xc, (li - B.first[cs]) % slots);
     if (b < 0)
         return;
+    const size_t nvox = (size_t)C.A.g.nx * C.A.g.ny * C.A.g.nz;
+    float *part = C.part ? C.part + range * nvox : nullptr;
     typename VS::T *const vs[1] = {(typename VS::T *)C.vol};
     switch (C.A.KV) {   // uniform over the workgroup
-    case 4: gather_brick<VS, 4, false>(C.A, b, C.ws, vs, lds); break;
-    case 2: gather_brick<VS, 2, false>(C.A, b, C.ws, vs, lds); break;
-    default: gather_brick<VS, 1, false>(C.A, b, C.ws, vs, lds); break;
+    case 4: gather_brick<VS, 4, false>(C.A, b, range, C.ws, vs, part, lds); break;
+    case 2: gather_brick<VS, 2, false>(C.A, b, range, C.ws, vs, part, lds); break;
+    default: gather_brick<VS, 1, false>(C.A, b, range, C.ws, vs, part, lds); break;
     }
 }
 
@@ -897,7 +929,7 @@ static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p, int C = 1)
     const int bk = 4 * p.KV;
     return BrickArgs{g, p.wins, even_width(p), p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
                      (g.ny + kAdjBJ - 1) / kAdjBJ, (g.nz + bk - 1) / bk, p.KV,   // WS: column stride
-                     windows_at_a_time(p, C), (int)window_area(p, C), 1.0f - adj_start_delta(g.nv)};
+                     windows_at_a_time(p, C), (int)window_area(p, C), p.split, 1.0f - adj_start_delta(g.nv)};
 }
 
 // The windows, the column ranges and the list of angles, or the final exchange
@@ -908,6 +940,17 @@ static size_t brick_lds(const AdjPlan &p, int C = 1)
                           kListAngles * sizeof(AngleEnt) / sizeof(float) + 4;
     const size_t exchange = (size_t)4 * 4 * 64 * p.KV;
     return std::max(gather, exchange) * sizeof(float);
+}
+
+// Words of the ranges' volumes of n voxels.
+static size_t part_words(const AdjPlan &p, size_t n) { return p.split > 1 ? n * p.split : 0; }
+
+template <class VS>
+static void launch_add_ranges(size_t n, int split, const float *part, typename VS::T *vol,
+                              hipStream_t s)
+{
+    hipLaunchKernelGGL(add_ranges<VS>, dim3((unsigned)((n + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, s, n, split, part, vol);
 }
 
 static hipError_t launch_ds_weight(const DevGeom &g, const void *sino, cbct_dtype st, float *ws,
@@ -988,10 +1031,11 @@ hipError_t launch_adjoint_brick(const DevGeom &g, const AdjPlan &p, const void *
                                 hipStream_t s)
 {
     BrickArgs A = brick_args(g, p);
-    dim3 grid(8 * slots_per_xcd(A), channels), block(kThreads);
-    const size_t nsino = (size_t)g.n_angles * g.nv * g.nu;
+    dim3 grid(8 * slots_per_xcd(A), channels, p.split), block(kThreads);
+    const size_t nsino = (size_t)g.n_angles * g.nv * g.nu * channels;
+    const size_t nvox = (size_t)g.nx * g.ny * g.nz * channels;
     ScratchLease lease;
-    hipError_t e = scratch_acquire(nsino * channels * sizeof(float), s, lease);
+    hipError_t e = scratch_acquire((nsino + part_words(p, nvox)) * sizeof(float), s, lease);
     if (e == hipSuccess)
         e = launch_ds_weight(g, sino, st, (float *)lease.ptr, channels, s);
     if (e == hipSuccess)
@@ -999,15 +1043,18 @@ hipError_t launch_adjoint_brick(const DevGeom &g, const AdjPlan &p, const void *
             using VS = decltype(vs);
             const size_t lds = brick_lds(p);
             const float *w = (const float *)lease.ptr;
+            float *part = p.split > 1 ? (float *)lease.ptr + nsino : nullptr;
             auto *x = (typename VS::T *)vol;
             if (adj_tall(p.KV, p.WS))
-                hipLaunchKernelGGL((adjoint_brick<VS, 4, true>), grid, block, lds, s, A, w, x);
+                hipLaunchKernelGGL((adjoint_brick<VS, 4, true>), grid, block, lds, s, A, w, x, part);
             else if (p.KV == 4)
-                hipLaunchKernelGGL((adjoint_brick<VS, 4, false>), grid, block, lds, s, A, w, x);
+                hipLaunchKernelGGL((adjoint_brick<VS, 4, false>), grid, block, lds, s, A, w, x, part);
             else if (p.KV == 2)
-                hipLaunchKernelGGL((adjoint_brick<VS, 2, false>), grid, block, lds, s, A, w, x);
+                hipLaunchKernelGGL((adjoint_brick<VS, 2, false>), grid, block, lds, s, A, w, x, part);
             else
-                hipLaunchKernelGGL((adjoint_brick<VS, 1, false>), grid, block, lds, s, A, w, x);
+                hipLaunchKernelGGL((adjoint_brick<VS, 1, false>), grid, block, lds, s, A, w, x, part);
+            if (part)
+                launch_add_ranges<VS>(nvox, p.split, part, x, s);
             return hipGetLastError();
         });
     const hipError_t r = scratch_release(s, lease);
@@ -1021,15 +1068,17 @@ hipError_t launch_adjoint_batch(int n, const cbct_geom *const *gs, const void *c
     B.n_cases = n;
     size_t lds = 0, total = 0;
     int items = 0;
-    size_t off[kMaxBatch];
+    size_t off[kMaxBatch], parts[kMaxBatch];
     for (int i = 0; i < n; ++i) {
         const cbct_geom *g = gs[i];
         B.first[i] = items;
-        B.c[i] = AdjCase{brick_args(g->dev, g->adj), nullptr, vols[i]};
-        items += slots_per_xcd(B.c[i].A);
+        B.c[i] = AdjCase{brick_args(g->dev, g->adj), nullptr, vols[i], nullptr};
+        items += slots_per_xcd(B.c[i].A) * g->adj.split;
         lds = std::max(lds, brick_lds(g->adj));
         off[i] = total;
         total += (size_t)g->dev.n_angles * g->dev.nv * g->dev.nu;
+        parts[i] = total;
+        total += part_words(g->adj, (size_t)g->dev.nx * g->dev.ny * g->dev.nz);
     }
     B.first[n] = items;
     B.n_items = items;
@@ -1038,12 +1087,18 @@ hipError_t launch_adjoint_batch(int n, const cbct_geom *const *gs, const void *c
     hipError_t e = scratch_acquire(total * sizeof(float), s, lease);
     for (int i = 0; i < n && e == hipSuccess; ++i) {
         B.c[i].ws = (const float *)lease.ptr + off[i];
+        if (gs[i]->adj.split > 1)
+            B.c[i].part = (float *)lease.ptr + parts[i];
         e = launch_ds_weight(gs[i]->dev, sinos[i], st, (float *)lease.ptr + off[i], 1, s);
     }
     if (e == hipSuccess)
         e = dispatch_storage(vt, st, [&](auto vs, auto) -> hipError_t {
             using VS = decltype(vs);
             hipLaunchKernelGGL((adjoint_batch<VS>), dim3(grid), dim3(kThreads), lds, s, B);
+            for (int i = 0; i < n; ++i)
+                if (B.c[i].part)
+                    launch_add_ranges<VS>((size_t)B.c[i].A.g.nx * B.c[i].A.g.ny * B.c[i].A.g.nz,
+                                          B.c[i].A.split, B.c[i].part, (typename VS::T *)vols[i], s);
             return hipGetLastError();
         });
     const hipError_t r = scratch_release(s, lease);

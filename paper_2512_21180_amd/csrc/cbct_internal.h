@@ -130,6 +130,7 @@ struct AdjPlan {
     int WS = 0;        // LDS column stride of the window (floats, 2 mod 4, > H)
     int NTmax = 0;     // largest row-tap count
     int KV = 4;        // voxels per thread along z: bricks are kAdjBI x kAdjBJ x 4 KV
+    int split = 1;     // ranges of angles gathered apart (few bricks), then added in order
     const BrickWin *wins = nullptr;   // device: [n_angles][nby][nbx]
 };
 
