@@ -145,6 +145,7 @@ struct GatherIn {
     uint2 range;        // per axis the lane's columns, from U0: first | last << 16
     float inv_rvs;
     float rbias;        // 1 - delta: run start floor(v_c + 1 - delta)
+    int eights;         // runs above 32 taps: their eights
 };
 
 __device__ inline float centre_x(const DevGeom &g, float i)
@@ -168,7 +169,8 @@ __device__ inline float centre_y(const DevGeom &g, float j)
 // convention's register budget and stack on the kernel.
 // C channels share a run's columns, rows and weights; their values lie side by
 // side in the window.
-template <int NT, int KV, int C>
+// LONG: runs of in.eights times NT taps.
+template <int NT, int KV, int C, bool LONG = false>
 __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[C][2][KV],
                                              float (&hi)[C][2][KV])
 {
@@ -224,31 +226,37 @@ __device__ __forceinline__ void gather_angle(const GatherIn &in, float (&lo)[C][
                 // the rounding of this difference of two large z indices small
                 float s = fmaf(t, fmaf(vsf - g.cv, g.rvs, g.rv0), KbK[n]);
                 const lds_float *py = lds_ptr((uint32_t)fmaf(vsf, 4.0f * C, colb));
-                float yv[NT][C];
-#pragma unroll
-                for (int m = 0; m < NT; ++m) {
-                    if constexpr (C == 4) {
-                        const f32x4 q = *(__attribute__((address_space(3))) const f32x4 *)(py + 4 * m);
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            yv[m][c] = q[c];
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < C; ++c)
-                            yv[m][c] = py[C * m + c];
-                    }
-                }
                 float csum[C];
 #pragma unroll
                 for (int c = 0; c < C; ++c)
                     csum[c] = 0.0f;
+                const int turns = LONG ? in.eights : 1;
+#pragma unroll 1
+                for (int e = 0; e < turns; ++e) {
+                    float yv[NT][C];
 #pragma unroll
-                for (int m = 0; m < NT; ++m) {
-                    const float hat = sat(1.0f - fabsf(s));
+                    for (int m = 0; m < NT; ++m) {
+                        if constexpr (C == 4) {
+                            const f32x4 q =
+                                *(__attribute__((address_space(3))) const f32x4 *)(py + 4 * m);
 #pragma unroll
-                    for (int c = 0; c < C; ++c)
-                        csum[c] = fmaf(hat, yv[m][c], csum[c]);
-                    s += beta;
+                            for (int c = 0; c < 4; ++c)
+                                yv[m][c] = q[c];
+                        } else {
+#pragma unroll
+                            for (int c = 0; c < C; ++c)
+                                yv[m][c] = py[C * m + c];
+                        }
+                    }
+#pragma unroll
+                    for (int m = 0; m < NT; ++m) {
+                        const float hat = sat(1.0f - fabsf(s));
+#pragma unroll
+                        for (int c = 0; c < C; ++c)
+                            csum[c] = fmaf(hat, yv[m][c], csum[c]);
+                        s += beta;
+                    }
+                    py += NT * C;
                 }
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
@@ -549,7 +557,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
         // compile-time tap count (NT rounded up to a supported count; extra
         // taps read zero weight)
         const GatherIn in{g, e.x_lo, e.x_hi, yt, (const float4 *)(yt + cols), HS, U0, V0, VS1,
-                          k0, {pl[0], pl[1]}, {sg[0], sg[1]}, range, inv_rvs, A.rbias};
+                          k0, {pl[0], pl[1]}, {sg[0], sg[1]}, range, inv_rvs, A.rbias, NT >> 3};
         if constexpr (C > 1) {   // at most 8 (see kMaxTapsMc)
             switch (NT) {
             case 4: gather_angle<4, KV, C>(in, lo, hi); break;
@@ -577,7 +585,8 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
             case 20: gather_angle<20, KV, C>(in, lo, hi); break;
             case 24: gather_angle<24, KV, C>(in, lo, hi); break;
             case 28: gather_angle<28, KV, C>(in, lo, hi); break;
-            default: gather_angle<32, KV, C>(in, lo, hi); break;
+            case 32: gather_angle<32, KV, C>(in, lo, hi); break;
+            default: gather_angle<8, KV, C, true>(in, lo, hi); break;
             }
         }
     };

@@ -76,7 +76,8 @@ constexpr int kSweepPad = 4;
 __host__ __device__ inline int sweep_pitch(int n) { return (n + 2 * kSweepPad + 3) & ~3; }
 
 // Row taps the adjoint reads per voxel and column: the needed count rounded
-// up to a count its kernel is instantiated for (4..16, 18, 20, 24, 28, 32).
+// up to a count its kernel is instantiated for (4..16, 18, 20, 24, 28, 32),
+// above 32 to a multiple of eight (read in eights).
 __host__ __device__ inline int adj_taps_rounded(int nt)
 {
     if (nt <= 4)
@@ -91,7 +92,9 @@ __host__ __device__ inline int adj_taps_rounded(int nt)
         return 24;
     if (nt <= 28)
         return 28;
-    return 32;
+    if (nt <= 32)
+        return 32;
+    return (nt + 7) & ~7;
 }
 
 // The adjoint's row runs start at floor(v_c + 1 - delta), v_c the row where a

@@ -41,7 +41,7 @@ constexpr int kBI = kAdjBI, kBJ = kAdjBJ;
 constexpr size_t kAdjLdsShare = 40 * 1024;    // four workgroups per CU
 constexpr size_t kAdjLdsBudget = 64 * 1024;
 constexpr long kMinBricks = 2 * 256;          // two bricks per CU
-constexpr int kMaxTaps = 32;      // row taps per voxel and column in the adjoint
+constexpr int kMaxTaps = 128;      // row taps per voxel and column in the adjoint
 
 struct TileBuild {
     std::vector<TileRec> tiles;

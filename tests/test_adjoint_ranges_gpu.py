@@ -41,3 +41,21 @@ def test_ranges_of_angles(dev, oracle, n_ang):
     b = cbct.adjoint(geo, yg[2].to(torch.bfloat16).contiguous())
     wide = cbct.adjoint(geo, yg[2].to(torch.bfloat16).float().contiguous())
     assert b.dtype == torch.bfloat16 and torch.equal(b, wide.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("nu,nv,width,n,vox", [(256, 64, 200.0, 37, 12.0), (256, 200, 200.0, 32, 8.0),
+                                               (160, 96, 200.0, 27, 16.0), (300, 200, 300.0, 22, 10.0),
+                                               (400, 32, 300.0, 39, 10.0), (256, 128, 200.0, 17, 12.0)])
+def test_long_runs_and_large_windows(dev, oracle, nu, nv, width, n, vox):
+    """Pixels far finer than voxels: runs of more than 32 rows per voxel, and
+    panel windows of 61 to 64 KB (with the list of angles and the column
+    ranges a workgroup takes up to 67 KB) or above, where the bricks give way
+    to one thread per voxel."""
+    torch, cbct = dev
+    print(f"[adjoint] large windows {nu}x{nv}", flush=True)
+    g = W.geometry(4, nu, nv, width / nu, width / nu, n, n, n // 2, vox)
+    geo = cbct.Geometry(g)
+    y = np.random.default_rng(nu).standard_normal(W.sino_shape(g)).astype(np.float32)
+    got = cbct.adjoint(geo, torch.tensor(y, device="cuda")).double().cpu().numpy()
+    ref = oracle.adjoint(g, y.astype(np.float64))
+    assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
