@@ -40,6 +40,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxR = 8;        // rays per thread
+constexpr int kFewR = 4;       // where there are few tiles (see the plan)
 constexpr int kBoxChunk = 256;  // planes whose boxes are tabulated at a time
 static_assert(kBoxChunk == kThreads, "the box table is filled one plane per thread");
 
@@ -100,6 +101,7 @@ __device__ __forceinline__ void sweep_tile_mc(const McGroup &M, const TileRec &T
     using V0 = typename VecOf<C>::T;
     constexpr int kSlots = L::kSlots;
     const DevGeom &g = M.g;
+    constexpr int NR = RC > 0 ? RC : kMaxR;
     const int R = RC > 0 ? RC : M.R, tub = M.tub;   // RC: rays per thread fixed at compile time
     const int tid = threadIdx.x;
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -108,9 +110,9 @@ __device__ __forceinline__ void sweep_tile_mc(const McGroup &M, const TileRec &T
     const int ul = min(uc, T.nu_t - 1);
     const ColRec c = g.cols[(size_t)T.a * g.nu + T.u0 + ul];
 
-    float kb[kMaxR], ks[kMaxR], acc[C][kMaxR];
+    float kb[NR], ks[NR], acc[C][NR];
 #pragma unroll
-    for (int r = 0; r < kMaxR; ++r) {
+    for (int r = 0; r < NR; ++r) {
         const int vr = T.v0 + min(row0 + min(r, R - 1), T.nv_t - 1);
         const float vz = g.rows[vr].x;
         kb[r] = fmaf(c.t0, vz, g.Kb);
@@ -231,7 +233,7 @@ __device__ __forceinline__ void sweep_tile_mc(const McGroup &M, const TileRec &T
         const int colz = (int)(lds_addr(buf) + (uint32_t)sizeof(V0) * (uint32_t)((int)qf - cb.qlo)) -
                          cb.klo * (int)(sizeof(V0) * QS);
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+        for (int r = 0; r < NR; ++r) {
             if (r < R) {
                 // as in the single-channel sweep: the exact fraction of the
                 // ray's z index and its row address from one floor conversion
@@ -263,17 +265,17 @@ __device__ __forceinline__ void sweep_tile_mc(const McGroup &M, const TileRec &T
         // eight registers throughout)
         int rb = row0;
         asm volatile("" : "+v"(rb));
-        float ds[kMaxR];
+        float ds[NR];
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r)
+        for (int r = 0; r < NR; ++r)
             ds[r] = g.rows[T.v0 + min(rb + r, T.nv_t - 1)].y;
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+        for (int r = 0; r < NR; ++r) {
             ds[r] = ray_ds(c.dsf, c.n2, ds[r]);
             asm volatile("" : "+v"(ds[r]));
         }
 #pragma unroll
-        for (int r = 0; r < kMaxR; ++r) {
+        for (int r = 0; r < NR; ++r) {
             const int vr = row0 + r;
             if (r < R && vr < T.nv_t) {
                 const size_t at = ((size_t)T.a * g.nv + T.v0 + vr) * g.nu + T.u0 + uc;
@@ -337,11 +339,15 @@ hipError_t launch_mc(const McArgs &B, hipStream_t s)
 {
     using L = McLayout<C, QS, ROWS>;
     const int grid = (B.n_items + 7) / 8 * 8;
-    bool all8 = true;   // every group's plan takes 8 rays per thread
-    for (int i = 0; i < B.n_groups; ++i)
+    bool all8 = true, all4 = true;   // every group's plan takes 8 (4) rays per thread
+    for (int i = 0; i < B.n_groups; ++i) {
         all8 = all8 && B.grp[i].R == kMaxR;
+        all4 = all4 && B.grp[i].R == kFewR;
+    }
     if (all8)
         hipLaunchKernelGGL((forward_mc<C, QS, ROWS, kMaxR>), dim3(grid), dim3(kThreads), L::kLds, s, B);
+    else if (all4)
+        hipLaunchKernelGGL((forward_mc<C, QS, ROWS, kFewR>), dim3(grid), dim3(kThreads), L::kLds, s, B);
     else
         hipLaunchKernelGGL((forward_mc<C, QS, ROWS, 0>), dim3(grid), dim3(kThreads), L::kLds, s, B);
     return hipGetLastError();
