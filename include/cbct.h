@@ -122,14 +122,15 @@ cbct_status cbct_geom_sizes(const cbct_geom *g, uint64_t *n_vox, uint64_t *n_sin
  * sino = A vol for n_channels >= 1 stacked channels.  vol (storage vt) is
  * [C][nz][ny][nx]; sino (storage st) is [C][n_angles][nv][nu].  Geometries
  * whose ray tiles spread over more voxels than the tiled kernel stages, or
- * whose volume channel with 64 more z planes reaches 4 GiB in FP32, run a
+ * whose volume channel with 64 more z planes, or with padded rows, reaches 4 GiB in FP32, run a
  * one-thread-per-ray
  * kernel with the same arithmetic (slower; cbct_geom_plan_info tells which).
- * The tiled kernel first writes the volume with x and y swapped (C x
- * nx*ny*nz elements of storage vt) into the device buffer the library owns
+ * The tiled kernel first writes two FP32 copies of the volume, as it is and
+ * with x and y swapped (C x nz (ny (nx + 8..11) + nx (ny + 8..11)) elements),
+ * into the device buffer the library owns
  * (the one cbct_adjoint uses: the first call on a device, or a larger one,
- * allocates; calls on different streams are ordered on it): tiles that
- * sweep x planes stage their boxes from it.  Multichannel FP32 stacks pack
+ * allocates; calls on different streams are ordered on it): its tiles stage
+ * their boxes from them.  Multichannel FP32 stacks pack
  * their channels there instead.
  */
 cbct_status cbct_forward(const cbct_geom *g, const void *vol, cbct_dtype vt,
@@ -142,7 +143,8 @@ cbct_status cbct_forward(const cbct_geom *g, const void *vol, cbct_dtype vt,
  * 64 KB of LDS even for 8 x 7 x 4 voxel bricks run a one-thread-per-voxel
  * kernel with the same weights (slower).
  * The bricked kernel first writes the projections times each ray's length
- * per plane (FP32, C x n_angles*nv*nu values) into a device buffer the
+ * per plane (FP32, C x n_angles*nv*nu values; for few bricks also up to eight
+ * partial volumes of C x nx*ny*nz) into a device buffer the
  * library owns, one per device, kept until the process ends and grown when
  * a call needs more: the first call on a device, and any larger one,
  * allocates (so it must not be the one captured into a graph).  Calls on
@@ -158,7 +160,7 @@ cbct_status cbct_adjoint(const cbct_geom *g, const void *sino, cbct_dtype st,
  * pointers), in one launch over all cases' work items (batches of more than
  * 16 cases run as one launch per 16 cases; cases whose geometry takes the
  * one-thread-per-ray kernel are launched on their own).  Like cbct_forward
- * it first writes each case's volume with x and y swapped into the
+ * it first writes two FP32 copies of each case's volume into the
  * library-owned device buffer.  Results are
  * bitwise identical to n separate cbct_forward calls.  With FP32 storage, cases that share one
  * handle (e.g. the channels of a stack, as in Alg. 1) are instead cut into
@@ -173,7 +175,10 @@ cbct_status cbct_batch_forward(int n, const cbct_geom *const *g, const void *con
 /* Batched adjoint, the counterpart of cbct_batch_forward: one launch per 16
  * cases whose geometry takes the bricked kernel (the others on their own).
  * It uses the same library-owned buffer as cbct_adjoint, sized for the
- * cases of one launch together. */
+ * cases of one launch together.  With FP32 storage, cases that share one
+ * handle are gathered in fours and twos where cbct_adjoint would gather the
+ * channels of a stack so (short windows and runs): the sums of separate calls, but
+ * for a run clamped at its window's edge by a row of weight at rounding level. */
 cbct_status cbct_batch_adjoint(int n, const cbct_geom *const *g, const void *const *sinos,
                                void *const *vols, cbct_dtype st, cbct_dtype vt, void *stream);
 

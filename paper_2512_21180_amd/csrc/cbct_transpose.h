@@ -1,4 +1,4 @@
-// Volume transpose for the forward sweeps: the tiles that sweep x planes
+// Volume copies for the forward sweeps: the tiles that sweep x planes
 // stage their boxes from a copy of the volume with x and y swapped, so that
 // a box row (fixed z, in-plane index y) is contiguous in memory.
 #pragma once
