@@ -177,8 +177,7 @@ cbct_status cbct_batch_forward(int n, const cbct_geom *const *g, const void *con
  * It uses the same library-owned buffer as cbct_adjoint, sized for the
  * cases of one launch together.  With FP32 storage, cases that share one
  * handle are gathered in fours and twos where cbct_adjoint would gather the
- * channels of a stack so (short windows and runs): the sums of separate calls, but
- * for a run clamped at its window's edge by a row of weight at rounding level. */
+ * channels of a stack so (short windows and runs).  The bits do not change. */
 cbct_status cbct_batch_adjoint(int n, const cbct_geom *const *g, const void *const *sinos,
                                void *const *vols, cbct_dtype st, cbct_dtype vt, void *stream);
 

@@ -82,6 +82,7 @@ struct BrickArgs {
     int area;              // LDS words of the windows
     int split;             // ranges of angles gathered apart
     float rbias;           // 1 - adj_start_delta(nv)
+    int plan_bk;           // layers of the plan's bricks (four channels take shorter ones)
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -464,8 +465,11 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
 
     // z extent of the brick's support (voxel centres +- one pitch), uniform
     const int kz0 = bz * kBK, kz1 = min(kz0 + kBK, g.nz) - 1;
-    const float zs0 = g.oz + ((float)kz0 - 0.5f * (float)(g.nz - 1)) * g.vz - g.vz;
-    const float zs1 = g.oz + ((float)kz1 - 0.5f * (float)(g.nz - 1)) * g.vz + g.vz;
+    auto support_z = [&](int k, int side) {
+        const float c = g.oz + ((float)k - 0.5f * (float)(g.nz - 1)) * g.vz;
+        return side < 0 ? c - g.vz : c + g.vz;
+    };
+    const float zs0 = support_z(kz0, -1), zs1 = support_z(kz1, 1);
     // the brick column's panel windows, one per angle (host FP64)
     const BrickWin *wcol = A.wins + (size_t)by * A.nbx + bx;
     const size_t wstep = (size_t)A.nbx * A.nby;
@@ -605,13 +609,36 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
                 const AngRec ar = g.angs[e.a];
                 const int U0 = (int)(bw.u01 & 0xffffu);
                 const int U1 = min((int)(bw.u01 >> 16), U0 + A.W - 1);
-                const float vmin =
-                    fmaf(fminf(bw.lmin * zs0, bw.lmax * zs0) - g.off_v, inv_dv, g.cv);
-                const float vmax =
-                    fmaf(fmaxf(bw.lmin * zs1, bw.lmax * zs1) - g.off_v, inv_dv, g.cv);
-                const int V0 = max((int)floorf(vmin) - 2, 0);
-                const int V1 = min(min((int)ceilf(vmax) + 2, g.nv - 1), V0 + A.H - 1);
+                auto window_rows = [&](float za, float zb, int &v0, int &v1) {
+                    const float vmin =
+                        fmaf(fminf(bw.lmin * za, bw.lmax * za) - g.off_v, inv_dv, g.cv);
+                    const float vmax =
+                        fmaf(fmaxf(bw.lmin * zb, bw.lmax * zb) - g.off_v, inv_dv, g.cv);
+                    v0 = max((int)floorf(vmin) - 2, 0);
+                    v1 = min(min((int)ceilf(vmax) + 2, g.nv - 1), v0 + A.H - 1);
+                };
+                int V0, V1;
+                window_rows(zs0, zs1, V0, V1);
                 seen = U0 <= U1 && V0 <= V1;
+                if constexpr (C == 4) {
+                    // A run starts at most NT - 1 rows below its window's last
+                    // row, and from another start its weights round
+                    // differently: for the bits of a single call the starts are
+                    // bounded by the window P0 .. P1 of the plan's brick that
+                    // holds this one.  So this window keeps the rows of P0 .. P1
+                    // that a run may take from its own start (at most one row
+                    // above the highest crossing of z index k - 1) or from the
+                    // bounded one.
+                    const int p0 = kz0 / A.plan_bk * A.plan_bk;
+                    const int p1 = min(p0 + A.plan_bk, g.nz) - 1;
+                    int P0, P1;
+                    window_rows(support_z(p0, -1), support_z(p1, 1), P0, P1);
+                    const float zc = zs1 - 2.0f * g.vz;
+                    const float vc =
+                        fmaf(fmaxf(bw.lmin * zc, bw.lmax * zc) - g.off_v, inv_dv, g.cv);
+                    V0 = min(V0, max(P1 - bw.nt + 1, P0));
+                    V1 = min(P1, max(V1, (int)floorf(vc) + 1 + bw.nt));
+                }
                 e.u01 = (uint32_t)U0 | (uint32_t)U1 << 16;
                 e.V0 = V0;
                 e.hn = (uint32_t)(V1 - V0 + 1) | (uint32_t)bw.nt << 16;
@@ -938,7 +965,8 @@ static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p, int C = 1)
     const int bk = 4 * p.KV;
     return BrickArgs{g, p.wins, even_width(p), p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
                      (g.ny + kAdjBJ - 1) / kAdjBJ, (g.nz + bk - 1) / bk, p.KV,   // WS: column stride
-                     windows_at_a_time(p, C), (int)window_area(p, C), p.split, 1.0f - adj_start_delta(g.nv)};
+                     windows_at_a_time(p, C), (int)window_area(p, C), p.split, 1.0f - adj_start_delta(g.nv),
+                     bk};
 }
 
 // The windows, the column ranges and the list of angles, or the final exchange
@@ -1001,6 +1029,7 @@ static hipError_t launch_mc(const cbct_geom *g, const float *const *sinos, float
     if (C == 4)
         p.KV = std::min(p.KV, 2);   // the plan's window holds the shorter bricks' too
     McAdjArgs<C> B{brick_args(d, p, C), ws, {}};
+    B.A.plan_bk = 4 * g->adj.KV;
     McSinos y{};
     for (int c = 0; c < C; ++c) {
         B.vol[c] = vols[c];

@@ -245,9 +245,8 @@ hipError_t launch_forward_mc(int n, const cbct_geom *const *g, const float *cons
                              float *const *sinos, int C, hipStream_t s);
 
 // Multichannel adjoint (cbct_adjoint.hip): C = 2 or 4 FP32 channels of one
-// geometry in one gather, the same sums as single-channel calls (a brick of
-// another height may clamp a run at its window's edge by a row of weight at
-// rounding level).
+// geometry in one gather, bitwise the sums of single-channel calls (the runs of
+// shorter bricks start where the plan's bricks start them).
 // adjoint_mc_channels: how many of `left` channels the next gather takes
 // together (1: none, the single-channel kernels).
 int adjoint_mc_channels(const cbct_geom *g, int left);
