@@ -178,7 +178,8 @@ __device__ inline float walk(const Grid &G, const float p[3], const float d[3], 
 // rounds to the end of the walk or below it steps out of the volume by one
 // voxel: the packed densities (one float2 per voxel, read through a buffer
 // resource) have a border of zeros for that; from the two separate volumes a
-// finished walk reads nothing.
+// march reads nothing once its crossings left along an axis have run out, or
+// its walk has ended.
 template <bool PACKED>
 __device__ inline float2 line_integrals(const Grid &G, const __amdgpu_buffer_rsrc_t &two,
                                         const float p[3], const float d[3], float tmax)
@@ -209,6 +210,7 @@ __device__ inline float2 line_integrals(const Grid &G, const __amdgpu_buffer_rsr
                                 kUnit * ((uint32_t)n[0] + kPad) * ((uint32_t)n[1] + kPad)};
     float tn[3], dt[3];
     uint32_t inc[3], off = PACKED ? stride[0] + stride[1] + stride[2] : 0u;
+    int left[3];   // crossings inside the volume (separate volumes only)
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         const float pe = fmaf(t0, d[q], p[q]), x = fmaf(tm, d[q], pe);
@@ -216,10 +218,10 @@ __device__ inline float2 line_integrals(const Grid &G, const __amdgpu_buffer_rsr
         off += (uint32_t)i * stride[q];
         const bool up = d[q] > 0.0f, on = d[q] != 0.0f;
         inc[q] = up ? stride[q] : 0u - stride[q];
+        left[q] = up ? n[q] - 1 - i : i;
         dt[q] = on ? v[q] * fabsf(inv[q]) : 0.0f;
         tn[q] = on ? (lo[q] + (float)(i + up) * v[q] - pe) * inv[q] : INFINITY;
     }
-    const uint32_t nvox = (uint32_t)n[0] * (uint32_t)n[1] * (uint32_t)n[2];
     const int steps = n[0] + n[1] + n[2] + 4;
     float t = 0.0f;   // from the entry point
 #pragma unroll 1
@@ -235,11 +237,16 @@ __device__ inline float2 line_integrals(const Grid &G, const __amdgpu_buffer_rsr
                 const auto b = __builtin_amdgcn_raw_buffer_load_b64(two, (int)off, 0, 0);
                 r[j] = make_float2(__uint_as_float(b[0]), __uint_as_float(b[1]));
             } else {
-                const bool in = len[j] != 0.0f && off < nvox;
+                const bool in = len[j] != 0.0f && (left[0] | left[1] | left[2]) >= 0;
                 r[j] = in ? make_float2(G.rw[off], G.rb[off]) : make_float2(0.0f, 0.0f);
             }
             const bool c0 = tn[0] <= to, c1 = tn[1] <= to, c2 = tn[2] <= to;
             off += (c0 ? inc[0] : 0u) + (c1 ? inc[1] : 0u) + (c2 ? inc[2] : 0u);
+            if constexpr (!PACKED) {
+                left[0] -= c0;
+                left[1] -= c1;
+                left[2] -= c2;
+            }
             tn[0] += c0 ? dt[0] : 0.0f;
             tn[1] += c1 ? dt[1] : 0.0f;
             tn[2] += c2 ? dt[2] : 0.0f;
