@@ -46,7 +46,8 @@
  *     s_T = sum_m (mu_m / mu_tot)(x) (mu_T,m / mu_tot,m)(e) dens_T,m(cos, e),
  *     p0 from the material line integrals from x to sigma, resp piecewise
  *     linear through (20, 5), (60, 20), (120, 10) keV, n the panel normal.
- *     The sum runs over records in order (deterministic).
+ *     The sum over records has a fixed order, set by n_rec and the panel's
+ *     size alone (deterministic).
  * Everything on the device is FP32; every pointer below except xs and the
  * handle is a device pointer owned by the caller.  Calls enqueue on `stream`.
  */
@@ -78,7 +79,16 @@ cbct_status cbct_scatter_paths(const cbct_geom *g, const float *rho, const cbct_
                                int n_scatter, float *rec, void *stream);
 
 /* Integrate n_rec records toward every pixel of g's panel at `angle`:
- * out [nv][nu] (overwritten), before the I_Sigma / |Src| scale. */
+ * out [nv][nu] (overwritten), before the I_Sigma / |Src| scale.
+ * The call first packs both densities, and on small panels sums chunks of the
+ * records apart, in a device buffer that the library owns: one per device for
+ * this call alone, kept until the process ends, of 8 bytes per voxel (with a
+ * border of one voxel; none where there are few records or 2^29 voxels) and
+ * 4 bytes per pixel and chunk (at most 64).  The first call, and one that
+ * needs more, allocates (and waits for the previous call's work to grow it);
+ * calls on different streams are ordered on the buffer.  Under stream capture,
+ * and where the memory cannot be had, the call does without: slower, the same
+ * bits. */
 cbct_status cbct_scatter_integrate(const cbct_geom *g, const float *rho, const cbct_xs *xs,
                                    int angle, int64_t n_rec, const float *rec, float *out,
                                    void *stream);

@@ -190,19 +190,23 @@ inline Col64 col_consts64(const cbct_geom_desc &d, double c, double s, int iu)
     return r;
 }
 
-// Library-owned device scratch (cbct_scratch.cpp): one buffer per device,
-// grown on demand.  scratch_acquire locks the device's buffer, makes stream s
-// wait for the previous user's work and returns the buffer in lease.ptr;
-// after enqueueing its work on s the caller must call scratch_release, which
-// records the completion event and unlocks.  Calls on different streams are
-// thereby ordered on the buffer; the first call (and any that needs a larger
-// buffer) allocates, so it must not run under stream capture.
+// Library-owned device scratch (cbct_scratch.cpp): per device one buffer for the
+// projector pair and one for the scatter integration, each grown on demand.
+// scratch_acquire locks the buffer, makes stream s wait for the previous
+// user's work and returns it in lease.ptr; after enqueueing its work on s the
+// caller must call scratch_release, which records the completion event and
+// unlocks.  Calls on different streams are thereby ordered on a buffer (and
+// the scatter integration is not ordered against the projectors); the first
+// call (and any that needs a larger buffer) allocates, so it must not run
+// under stream capture.
+enum ScratchUse { kScratchProjector = 0, kScratchScatter = 1 };
 struct ScratchLease {
     void *ptr = nullptr;
-    int device = -1;
+    int slot = -1;   // device and use
     std::unique_lock<std::mutex> lock;
 };
-hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease);
+hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease,
+                           ScratchUse use = kScratchProjector);
 hipError_t scratch_release(hipStream_t s, ScratchLease &lease);
 
 // Plans (cbct_plan.cpp): host FP64 analysis of tile boxes and brick

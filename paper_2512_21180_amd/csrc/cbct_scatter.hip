@@ -16,8 +16,8 @@
 // centre gives the two material line integrals, from which the escape
 // probabilities at the incoming and the Compton energy follow by linearity.
 // Each pixel's 8 phase sums are added in phase order, and where the records
-// are cut into chunks (one workgroup per tile and chunk) the chunks' sums in
-// chunk order: deterministic.
+// are cut into chunks (a workgroup per tile takes one of them, or all in turn)
+// the chunks' sums in chunk order: deterministic, and the same by every route.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -386,8 +386,9 @@ struct IntArgs {
     long nrec;
     const float *rec;        // [nrec][8]
     const float2 *two;       // both densities per voxel, or null
-    int tiles_u, chunks;     // pixel tiles along u, chunks of the records
-    float *out;              // [chunks][nv][nu]
+    int tiles_u;             // pixel tiles along u
+    int chunks, per;         // chunks of the records, and how many a workgroup adds up
+    float *out;              // [chunks / per][nv][nu]
 };
 
 // One workgroup: 8 x 8 pixels x 8 record phases, one phase per wave (wave p
@@ -405,7 +406,7 @@ constexpr int kPixEdge = 8, kPixTile = kPixEdge * kPixEdge, kPhases = 8;
 template <bool PACKED>
 __global__ void __launch_bounds__(kPixTile * kPhases, 6) k_scatter_integrate(IntArgs A)
 {
-    __shared__ float part[kPhases][kPixTile];
+    __shared__ float part[kPhases][kPixTile], total[kPixTile];
     const int lane = threadIdx.x % kPixTile;
     const int ph = __builtin_amdgcn_readfirstlane(threadIdx.x / kPixTile);
     const int iu = (blockIdx.x % A.tiles_u) * kPixEdge + lane % kPixEdge;
@@ -418,58 +419,66 @@ __global__ void __launch_bounds__(kPixTile * kPhases, 6) k_scatter_integrate(Int
         kBufferWord3);
     const float pu = ((float)iu - A.cu) * A.du, pv = ((float)iv - A.cv) * A.dv;
     const float P[3] = {fmaf(pu, A.eux, A.Dx), fmaf(pu, A.euy, A.Dy), A.Dz + pv};
-    float acc = 0.0f;
-    for (long r = ph + kPhases * blockIdx.y; r < A.nrec; r += kPhases * A.chunks) {
-        const float *q = A.rec + 8 * r;
-        const float w = q[7];
-        if (!(w > 0.0f) || !live)
-            continue;
-        const float x[3] = {q[0], q[1], q[2]};
-        const float e = q[6];
-        float vs[3] = {P[0] - x[0], P[1] - x[1], P[2] - x[2]};
-        const float r2 = fmaf(vs[0], vs[0], fmaf(vs[1], vs[1], vs[2] * vs[2]));
-        const float dist = sqrtf(r2);
-        const float id = 1.0f / dist;
-        vs[0] *= id;
-        vs[1] *= id;
-        vs[2] *= id;
-        const float cth = fmaf(q[3], vs[0], fmaf(q[4], vs[1], q[5] * vs[2]));
-        const float ec = e / (1.0f + e * (1.0f - cth) / kMeC2);
-        const float2 path = line_integrals<PACKED>(G, two, x, vs, dist);
-        int k, kc;
-        float f, fc;
-        e_pos(X, e, k, f);
-        k = __builtin_amdgcn_readfirstlane(k);   // one energy per record
-        e_pos(X, ec, kc, fc);
-        const float mw = mu_tot(X, 0, k, f), mb = mu_tot(X, 1, k, f);
-        const long vi = voxel_at(G, x[0], x[1], x[2]);
-        const float aw = vi >= 0 ? G.rw[vi] * mw : 0.0f, ab = vi >= 0 ? G.rb[vi] * mb : 0.0f;
-        const float tot = aw + ab;
-        const float fm[2] = {tot > 0.0f ? aw / tot : 1.0f, tot > 0.0f ? ab / tot : 0.0f};
-        const float sd = (cth + 1.0f) * 0.5f * (float)(X.I - 1);
-        float sc = 0.0f, sr = 0.0f;
-        for (int m = 0; m < 2; ++m) {
-            const float mt = m == 0 ? mw : mb;
-            sc = fmaf(fm[m] * mu_kind(X, m, 1, k, f) / mt,
-                      table2(X.dens + (m * 2 + 0) * X.K * X.I, X.I, k, f, sd), sc);
-            sr = fmaf(fm[m] * mu_kind(X, m, 2, k, f) / mt,
-                      table2(X.dens + (m * 2 + 1) * X.K * X.I, X.I, k, f, sd), sr);
+    const int per = PACKED ? 1 : A.per;   // packed: a workgroup for every chunk
+    const int c0 = blockIdx.y * per;
+    for (int c = c0; c < c0 + per; ++c) {
+        float acc = 0.0f;
+        for (long r = ph + kPhases * c; r < A.nrec; r += kPhases * A.chunks) {
+            const float *q = A.rec + 8 * r;
+            const float w = q[7];
+            if (!(w > 0.0f) || !live)
+                continue;
+            const float x[3] = {q[0], q[1], q[2]};
+            const float e = q[6];
+            float vs[3] = {P[0] - x[0], P[1] - x[1], P[2] - x[2]};
+            const float r2 = fmaf(vs[0], vs[0], fmaf(vs[1], vs[1], vs[2] * vs[2]));
+            const float dist = sqrtf(r2);
+            const float id = 1.0f / dist;
+            vs[0] *= id;
+            vs[1] *= id;
+            vs[2] *= id;
+            const float cth = fmaf(q[3], vs[0], fmaf(q[4], vs[1], q[5] * vs[2]));
+            const float ec = e / (1.0f + e * (1.0f - cth) / kMeC2);
+            const float2 path = line_integrals<PACKED>(G, two, x, vs, dist);
+            int k, kc;
+            float f, fc;
+            e_pos(X, e, k, f);
+            k = __builtin_amdgcn_readfirstlane(k);   // one energy per record
+            e_pos(X, ec, kc, fc);
+            const float mw = mu_tot(X, 0, k, f), mb = mu_tot(X, 1, k, f);
+            const long vi = voxel_at(G, x[0], x[1], x[2]);
+            const float aw = vi >= 0 ? G.rw[vi] * mw : 0.0f, ab = vi >= 0 ? G.rb[vi] * mb : 0.0f;
+            const float tot = aw + ab;
+            const float fm[2] = {tot > 0.0f ? aw / tot : 1.0f, tot > 0.0f ? ab / tot : 0.0f};
+            const float sd = (cth + 1.0f) * 0.5f * (float)(X.I - 1);
+            float sc = 0.0f, sr = 0.0f;
+            for (int m = 0; m < 2; ++m) {
+                const float mt = m == 0 ? mw : mb;
+                sc = fmaf(fm[m] * mu_kind(X, m, 1, k, f) / mt,
+                          table2(X.dens + (m * 2 + 0) * X.K * X.I, X.I, k, f, sd), sc);
+                sr = fmaf(fm[m] * mu_kind(X, m, 2, k, f) / mt,
+                          table2(X.dens + (m * 2 + 1) * X.K * X.I, X.I, k, f, sd), sr);
+            }
+            const float p0c =
+                expf(-fmaf(mu_tot(X, 0, kc, fc), path.x, mu_tot(X, 1, kc, fc) * path.y));
+            const float p0r = expf(-fmaf(mw, path.x, mb * path.y));
+            const float s = fmaf(sc * p0c, resp(ec), sr * p0r * resp(e));
+            const float cn = fabsf(fmaf(A.nx_, vs[0], A.ny_ * vs[1]));
+            acc = fmaf(s * w * cn, A.du * A.dv / r2, acc);
         }
-        const float p0c =
-            expf(-fmaf(mu_tot(X, 0, kc, fc), path.x, mu_tot(X, 1, kc, fc) * path.y));
-        const float p0r = expf(-fmaf(mw, path.x, mb * path.y));
-        const float s = fmaf(sc * p0c, resp(ec), sr * p0r * resp(e));
-        const float cn = fabsf(fmaf(A.nx_, vs[0], A.ny_ * vs[1]));
-        acc = fmaf(s * w * cn, A.du * A.dv / r2, acc);
+        part[ph][lane] = acc;
+        __syncthreads();
+        if (ph == 0) {
+            float v = part[0][lane];
+            for (int k = 1; k < kPhases; ++k)
+                v += part[k][lane];
+            total[lane] = c == c0 ? v : total[lane] + v;
+        }
+        if (per > 1)
+            __syncthreads();   // the sums are read before the next chunk's
     }
-    part[ph][lane] = acc;
-    __syncthreads();
-    if (ph == 0 && live) {
-        float v = part[0][lane];
-        for (int k = 1; k < kPhases; ++k)
-            v += part[k][lane];
-        A.out[((size_t)blockIdx.y * A.nv + iv) * A.nu + iu] = v;
-    }
+    if (ph == 0 && live)
+        A.out[((size_t)blockIdx.y * A.nv + iv) * A.nu + iu] = total[lane];
 }
 
 // The packed densities: [nz + 2][ny + 2][nx + 2] pairs, zero on the border.
@@ -613,7 +622,6 @@ extern "C" cbct_status cbct_scatter_integrate(const cbct_geom *g, const float *r
     A.tiles_u = (d.nu + kPixEdge - 1) / kPixEdge;
     const unsigned tiles =
         (unsigned)A.tiles_u * (unsigned)((d.nv + kPixEdge - 1) / kPixEdge);
-    A.chunks = 1;
     A.two = nullptr;
     hipStream_t st = (hipStream_t)stream;
     const size_t nvox = (size_t)d.nx * d.ny * d.nz;
@@ -628,21 +636,24 @@ extern "C" cbct_status cbct_scatter_integrate(const cbct_geom *g, const float *r
     const bool pack = npad < ((size_t)1 << 29) && (size_t)n_rec * npix >= nvox / 16;
     const size_t vb = pack ? npad * sizeof(float2) : 0;
     const size_t pb = chunks > 1 ? (size_t)chunks * npix * sizeof(float) : 0;
-    // both live in the library's buffer; under stream capture (where that
-    // buffer can neither grow nor be waited for) and where it cannot be had
-    // the marches read the caller's volumes and one workgroup takes all records
+    // both live in a buffer that the library owns; under stream capture (where
+    // it can neither grow nor be waited for) and where it cannot be had the
+    // marches read the caller's volumes and a workgroup takes its tile's chunks
+    // in turn: more slowly, and bitwise the same image
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     ScratchLease lease;
     bool leased = false;
     if (vb + pb > 0 && hipStreamIsCapturing(st, &cap) == hipSuccess &&
         cap == hipStreamCaptureStatusNone) {
-        leased = scratch_acquire(vb + pb, st, lease) == hipSuccess;
+        leased = scratch_acquire(vb + pb, st, lease, kScratchScatter) == hipSuccess;
         if (!leased) {
             (void)hipGetLastError();
             (void)scratch_release(st, lease);
         }
     }
     const dim3 block(kPixTile * kPhases);
+    A.chunks = chunks;
+    A.per = leased ? 1 : chunks;
     if (leased) {
         float *part = (float *)((char *)lease.ptr + vb);
         if (pack) {
@@ -650,7 +661,6 @@ extern "C" cbct_status cbct_scatter_integrate(const cbct_geom *g, const float *r
             hipLaunchKernelGGL(k_pack_two, dim3((unsigned)((npad + kT - 1) / kT)), dim3(kT), 0, st,
                                A.G, (float2 *)lease.ptr);
         }
-        A.chunks = chunks;
         A.out = chunks > 1 ? part : out;
         if (pack)
             hipLaunchKernelGGL(k_scatter_integrate<true>, dim3(tiles, chunks), block, 0, st, A);

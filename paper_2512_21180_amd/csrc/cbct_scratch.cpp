@@ -1,5 +1,5 @@
-// Library-owned device scratch, one buffer per device, reused across calls
-// (see cbct_internal.h).  A call takes the device's buffer under a lock,
+// Library-owned device scratch, one buffer per device and use, reused across
+// calls (see cbct_internal.h).  A call takes the buffer under a lock,
 // makes its stream wait for the previous user's completion event, enqueues
 // its work and records the event again before releasing the lock, so calls
 // on different streams never overlap on the buffer.  The buffer grows (once,
@@ -13,7 +13,7 @@
 namespace cbct {
 namespace {
 
-constexpr int kMaxDevices = 64;
+constexpr int kMaxDevices = 64, kUses = 2;
 
 struct DevScratch {
     void *ptr = nullptr;
@@ -21,12 +21,12 @@ struct DevScratch {
     hipEvent_t last = nullptr;   // completion of the latest user's work
 };
 
-std::mutex g_mutex[kMaxDevices];
-DevScratch g_scratch[kMaxDevices];
+std::mutex g_mutex[kMaxDevices * kUses];
+DevScratch g_scratch[kMaxDevices * kUses];
 
 }  // namespace
 
-hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease)
+hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease, ScratchUse use)
 {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -34,9 +34,9 @@ hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease)
         return e;
     if (dev < 0 || dev >= kMaxDevices)
         return hipErrorInvalidDevice;
-    lease.lock = std::unique_lock<std::mutex>(g_mutex[dev]);
-    lease.device = dev;
-    DevScratch &S = g_scratch[dev];
+    lease.slot = dev * kUses + use;
+    lease.lock = std::unique_lock<std::mutex>(g_mutex[lease.slot]);
+    DevScratch &S = g_scratch[lease.slot];
     if (!S.last) {
         e = hipEventCreateWithFlags(&S.last, hipEventDisableTiming);
         if (e != hipSuccess)
@@ -71,10 +71,10 @@ hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease)
 hipError_t scratch_release(hipStream_t s, ScratchLease &lease)
 {
     hipError_t e = hipSuccess;
-    if (lease.device >= 0 && g_scratch[lease.device].last)
-        e = hipEventRecord(g_scratch[lease.device].last, s);
+    if (lease.slot >= 0 && g_scratch[lease.slot].last)
+        e = hipEventRecord(g_scratch[lease.slot].last, s);
     lease.ptr = nullptr;
-    lease.device = -1;
+    lease.slot = -1;
     if (lease.lock.owns_lock())
         lease.lock.unlock();
     return e;

@@ -1,0 +1,60 @@
+"""The scatter integration gives the same bits by every route: packed densities
+and chunks of the records side by side in the library's buffer, or, where that
+buffer cannot be used (under stream capture), the caller's volumes and the
+chunks in turn."""
+import numpy as np
+import pytest
+
+from paper_2512_21180_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    from paper_2512_21180_amd import cbct
+    return torch, cbct
+
+
+def _records(n, seed, span):
+    r = np.random.default_rng(seed)
+    rec = np.zeros((n, 8), dtype=np.float32)
+    rec[:, :3] = r.uniform(-1.0, 1.0, (n, 3)) * np.array(span)
+    d = r.standard_normal((n, 3)) - np.array([1.5, 0.0, 0.0])
+    rec[:, 3:6] = d / np.linalg.norm(d, axis=1, keepdims=True)
+    rec[:, 6] = r.uniform(25.0, 115.0, n)
+    rec[:, 7] = r.uniform(0.05, 1.0, n)
+    return rec
+
+
+def _captured(torch, cbct, geo, rho, X, rec, ref):
+    out = torch.empty_like(ref)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cbct.scatter_integrate(geo, rho, X, 0, rec, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        yield out
+
+
+# one chunk; chunks of records with a remainder; more chunks than a phase has records
+@pytest.mark.parametrize("nu,nv,n", [(9, 7, 20), (17, 33, 45), (33, 17, 300), (8, 8, 31)])
+def test_routes_same_bits(dev, nu, nv, n):
+    torch, cbct = dev
+    print(f"[scatter] bits {nu}x{nv}, {n} records", flush=True)
+    g = W.geometry(4, nu, nv, 400.0 / nu, 300.0 / nv, 41, 41, 30, 6.0)
+    rho = np.abs(np.random.default_rng(n).standard_normal((2, 30, 41, 41))).astype(np.float32)
+    geo, X = cbct.Geometry(g), cbct.ScatterTables(W.scatter_tables(), "cuda")
+    rho_g = torch.tensor(rho, device="cuda")
+    rec = torch.tensor(_records(n, nu, (110.0, 110.0, 80.0)), device="cuda")
+    ref = cbct.scatter_integrate(geo, rho_g, X, 0, rec)
+    assert ref.abs().max() > 0
+    for out in _captured(torch, cbct, geo, rho_g, X, rec, ref):
+        assert torch.equal(out, ref)
