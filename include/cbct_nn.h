@@ -125,7 +125,10 @@ cbct_status cbct_upsample(int r, int n0, int n1, int n2, const float *in, float 
  * the same size (receives the filtered projections); vol: FP32
  * [nz][ny][nx].  The angles must be a full orbit of equally spaced angles
  * (else CBCT_E_ARG); nu <= 4096 (else CBCT_E_SHAPE); an offset panel must
- * overlap the central ray (else CBCT_E_GEOM).  FP32 arithmetic.
+ * overlap the central ray (else CBCT_E_GEOM).  FP32 arithmetic.  An infinite
+ * or undefined pixel leaves the filtered row finite where the Ram-Lak kernel
+ * is zero (an even number of columns away) and takes the whole row under the
+ * Hann window.
  */
 cbct_status cbct_fdk(const cbct_geom *g, const float *sino, int window, float *work,
                      float *vol, void *stream);

@@ -104,11 +104,13 @@ __global__ void __launch_bounds__(kT) k_fdk_filter(FdkArgs A, const float *p, fl
 
 // The filter as a matrix product: out[r][j] = sum_k in[r][k] h[k - j] over the
 // weighted rows, on v_mfma_f32_16x16x4_f32 (FP32 operands and sums).  A
-// workgroup holds 16 WM whole rows in LDS (33 KB: four workgroups per CU);
+// workgroup holds 16 WM whole rows in LDS (37 KB with the table: four per CU);
 // a wave forms 16 rows x 128 columns in eight accumulators, so each row
 // operand serves eight products, and reads the Toeplitz operand as 64
 // consecutive words of the kernel's table.  Whole rows are read before any
-// is written, as the one-row kernel does, so `q` may be `p`.  Bound by the
+// is written, as the one-row kernel does, so `q` may be `p`.  A row with an
+// infinite or undefined value is summed directly instead: in the product the
+// ramp's zeros would spread it over the even offsets.  Bound by the
 // matrix cores: 2 nu operations per output, half of them on the ramp's zeros
 // (splitting columns by parity would save those, but not under the Hann
 // window).  184320 rows of 512: 4.33 ms by direct sums from LDS (two reads
@@ -121,12 +123,25 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // lanes mod 16, k on lanes / 16) falls on 64 different banks.
 __host__ __device__ inline int mm_stride(int nu) { return (nu + 63) / 64 * 64 + 4; }
 
+// The ramp output at column j of a weighted row, as `k_fdk_filter` sums it:
+// odd offsets only, nothing read off the row.
+__device__ inline float ramp_direct(const float *row, int nu, int j)
+{
+    float acc = 0.0f;
+    for (int n = 1; n <= nu; n += 2) {
+        const float l = j - n >= 0 ? row[j - n] : 0.0f, r = j + n < nu ? row[j + n] : 0.0f;
+        acc = fmaf(1.0f / (9.869604401089358f * (float)n * (float)n), l + r, acc);
+    }
+    return fmaf(0.25f, j >= 0 && j < nu ? row[j] : 0.0f, -acc);
+}
+
 template <int WM>
 __global__ void __launch_bounds__(kT) k_fdk_filter_mm(FdkArgs A, int rows, const float *p, float *q)
 {
     constexpr int WN = 4 / WM;
     constexpr int kN = kMmN * WN, kCols = kN / 64;   // columns formed, per lane when staging
     extern __shared__ float lds[];
+    __shared__ uint32_t unbounded[4];   // per wave: its rows with an infinite or undefined value
     const DevGeom &g = A.g;
     const int nu = g.nu, S = mm_stride(nu), K = (nu + 3) & ~3;
     float *h = lds + 16 * WM * S;    // h[d + kN], d = k - j
@@ -150,6 +165,7 @@ __global__ void __launch_bounds__(kT) k_fdk_filter_mm(FdkArgs A, int rows, const
             ui[m] = u * (A.R / A.D);
             rw[m] = red_weight(A, u);
         }
+        uint32_t bad = 0u;
 #pragma unroll
         for (int k = 0; k < 4 * WM; ++k) {
             const int row = w + 4 * k, rr = r0 + row;   // uniform
@@ -163,12 +179,38 @@ __global__ void __launch_bounds__(kT) k_fdk_filter_mm(FdkArgs A, int rows, const
 #pragma unroll
             for (int m = 0; m < kCols; ++m) {
                 const float cw = A.R * rsqrtf(fmaf(A.R, A.R, fmaf(ui[m], ui[m], vi * vi)));
+                x[m] = lane + 64 * m < nu ? x[m] * rw[m] * cw : 0.0f;
                 if (lane + 64 * m < S)
-                    lds[row * S + lane + 64 * m] = lane + 64 * m < nu ? x[m] * rw[m] * cw : 0.0f;
+                    lds[row * S + lane + 64 * m] = x[m];
             }
+            bool finite = true;
+#pragma unroll
+            for (int m = 0; m < kCols; ++m)
+                finite = finite && fabsf(x[m]) < INFINITY;
+            bad |= __any(!finite) ? 1u << k : 0u;
         }
+        if (lane == 0)
+            unbounded[w] = bad;
     }
     __syncthreads();
+    const float scale = 1.0f / A.dui;  // du_i * h, h ~ 1 / du_i^2
+    uint32_t skip[4], some = 0u;   // row r is bit r / 4 of skip[r % 4]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        skip[i] = __builtin_amdgcn_readfirstlane(unbounded[i]);
+        some |= skip[i];
+    }
+    if (some)
+        for (int row = 0; row < 16 * WM; ++row)
+            if (unbounded[row & 3] >> (row >> 2) & 1u)
+                for (int j = threadIdx.x; j < nu; j += kT) {
+                    const float *x = lds + row * S;
+                    float v = ramp_direct(x, nu, j);
+                    if (A.hann)
+                        v = fmaf(0.5f, v,
+                                 0.25f * (ramp_direct(x, nu, j - 1) + ramp_direct(x, nu, j + 1)));
+                    q[(size_t)(r0 + row) * nu + j] = scale * v;
+                }
     const int wm = w / WN, j0 = (w % WN) * kMmN;
     if (j0 >= nu)
         return;
@@ -184,14 +226,13 @@ __global__ void __launch_bounds__(kT) k_fdk_filter_mm(FdkArgs A, int rows, const
         for (int t = 0; t < 8; ++t)
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[k - 16 * t], acc[t], 0, 0, 0);
     }
-    const float scale = 1.0f / A.dui;  // du_i * h, h ~ 1 / du_i^2
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
         const int j = j0 + 16 * t + (lane & 15);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int rr = r0 + 16 * wm + 4 * (lane >> 4) + r;
-            if (j < nu && rr < rows)
+            const int row = 16 * wm + 4 * (lane >> 4) + r, rr = r0 + row;
+            if (j < nu && rr < rows && !(skip[r] >> (row >> 2) & 1u))
                 q[(size_t)rr * nu + j] = scale * acc[t][r];
         }
     }
