@@ -149,7 +149,9 @@ cbct_status cbct_forward(const cbct_geom *g, const void *vol, cbct_dtype vt,
  * a call needs more: the first call on a device, and any larger one,
  * allocates (so it must not be the one captured into a graph).  Calls on
  * different streams are ordered on that buffer (each waits for the previous
- * call's work); allocation failure returns CBCT_E_HIP.
+ * call's work); allocation failure returns CBCT_E_HIP.  A buffer that a
+ * captured call used stays allocated when a later call outgrows it, so its
+ * graph may be replayed; replays are ordered on their own stream only.
  */
 cbct_status cbct_adjoint(const cbct_geom *g, const void *sino, cbct_dtype st,
                          void *vol, cbct_dtype vt, int n_channels, void *stream);

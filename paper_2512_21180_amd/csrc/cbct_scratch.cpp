@@ -3,7 +3,9 @@
 // makes its stream wait for the previous user's completion event, enqueues
 // its work and records the event again before releasing the lock, so calls
 // on different streams never overlap on the buffer.  The buffer grows (once,
-// after the previous user has finished) when a call needs more.
+// after the previous user has finished) when a call needs more; an outgrown
+// buffer is freed unless a captured call used it, whose graph names it for as
+// long as it may be replayed.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -18,6 +20,7 @@ constexpr int kMaxDevices = 64, kUses = 2;
 struct DevScratch {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool captured = false;       // a graph may name the buffer
     hipEvent_t last = nullptr;   // completion of the latest user's work
 };
 
@@ -51,9 +54,10 @@ hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease, Scr
             e = hipEventSynchronize(S.last);
             if (e != hipSuccess)
                 return e;
-            e = hipFree(S.ptr);
+            e = S.captured ? hipSuccess : hipFree(S.ptr);
             S.ptr = nullptr;
             S.bytes = 0;
+            S.captured = false;
             if (e != hipSuccess)
                 return e;
         }
@@ -64,6 +68,11 @@ hipError_t scratch_acquire(size_t bytes, hipStream_t s, ScratchLease &lease, Scr
         }
         S.bytes = bytes;
     }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess)
+        (void)hipGetLastError();   // the null stream beside another stream's capture
+    else if (cap != hipStreamCaptureStatusNone)
+        S.captured = true;
     lease.ptr = S.ptr;
     return hipSuccess;
 }
