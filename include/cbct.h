@@ -125,8 +125,9 @@ cbct_status cbct_geom_sizes(const cbct_geom *g, uint64_t *n_vox, uint64_t *n_sin
  * whose volume channel with 64 more z planes, or with padded rows, reaches 4 GiB in FP32, run a
  * one-thread-per-ray
  * kernel with the same arithmetic (slower; cbct_geom_plan_info tells which).
- * The tiled kernel first writes two FP32 copies of the volume, as it is and
- * with x and y swapped (C x nz (ny (nx + 8..11) + nx (ny + 8..11)) elements),
+ * The tiled kernel first writes FP32 copies of the volume, as it is for rays
+ * that sample y planes and with x and y swapped for those that sample x planes
+ * (both but for a few projections: C x nz (ny (nx + 8..11) + nx (ny + 8..11)) elements),
  * into the device buffer the library owns
  * (the one cbct_adjoint uses: the first call on a device, or a larger one,
  * allocates; calls on different streams are ordered on it): its tiles stage
@@ -162,7 +163,7 @@ cbct_status cbct_adjoint(const cbct_geom *g, const void *sino, cbct_dtype st,
  * pointers), in one launch over all cases' work items (batches of more than
  * 16 cases run as one launch per 16 cases; cases whose geometry takes the
  * one-thread-per-ray kernel are launched on their own).  Like cbct_forward
- * it first writes two FP32 copies of each case's volume into the
+ * it first writes FP32 copies of each case's volume into the
  * library-owned device buffer.  Results are
  * bitwise identical to n separate cbct_forward calls.  With FP32 storage, cases that share one
  * handle (e.g. the channels of a stack, as in Alg. 1) are instead cut into

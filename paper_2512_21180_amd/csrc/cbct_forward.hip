@@ -367,10 +367,10 @@ hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *
     // buffer, for the tiles that sweep x planes (and for 16-bit volumes)
     ScratchLease lease;
     hipError_t e = scratch_acquire(
-        sweep_words(g.nx, g.ny, (size_t)g.nz * channels) * sizeof(float), s, lease);
+        sweep_words(g.nx, g.ny, (size_t)g.nz * channels, p.axes) * sizeof(float), s, lease);
     if (e == hipSuccess) {
         const SweepVolumes v =
-            make_sweep_volumes(vol, vt, (float *)lease.ptr, g.nx, g.ny, g.nz * channels, s);
+            make_sweep_volumes(vol, vt, (float *)lease.ptr, g.nx, g.ny, g.nz * channels, p.axes, s);
         e = dispatch_storage(vt, st, [&](auto, auto ss) -> hipError_t {
             using SS = decltype(ss);
             auto *y = (typename SS::T *)sino;
@@ -401,7 +401,7 @@ hipError_t launch_forward_batch(int n, const cbct_geom *const *gs, const void *c
                          g->fwd.n_tiles, nullptr, nullptr, sinos[i]};
         items += g->fwd.n_tiles;
         off[i] = total;
-        total += (sweep_words(g->dev.nx, g->dev.ny, g->dev.nz) + 63) & ~(size_t)63;
+        total += (sweep_words(g->dev.nx, g->dev.ny, g->dev.nz, g->fwd.axes) + 63) & ~(size_t)63;
     }
     B.first[n] = items;
     B.n_items = items;
@@ -412,7 +412,7 @@ hipError_t launch_forward_batch(int n, const cbct_geom *const *gs, const void *c
         for (int i = 0; i < n; ++i) {
             const DevGeom &d = gs[i]->dev;
             const SweepVolumes v = make_sweep_volumes(vols[i], vt, (float *)lease.ptr + off[i],
-                                                      d.nx, d.ny, d.nz, s);
+                                                      d.nx, d.ny, d.nz, gs[i]->fwd.axes, s);
             B.c[i].vol = v.vol;
             B.c[i].volt = v.volt;
         }

@@ -66,6 +66,7 @@ struct FwdPlan {
                        // tiles are TU x (256 / TU) R rays
     int BQ = 0, BK = 0;
     int n_tiles = 0;   // padded to a multiple of 8 (padding tiles have nu_t = 0)
+    int axes = 0;      // sampling axes of the tiles that meet the volume: 1 x planes, 2 y planes
     const TileRec *tiles = nullptr;   // device
 };
 

@@ -311,6 +311,9 @@ void plan_host(cbct_geom *g)
         g->fwd.BQ = tb.BQ;
         g->fwd.BK = tb.BK;
         g->fwd.n_tiles = (int)tb.tiles.size();
+        for (const TileRec &t : tb.tiles)
+            if (t.p_lo <= t.p_hi)
+                g->fwd.axes |= t.cls == 0 ? 1 : 2;
         g->tiles = std::move(tb.tiles);
     }
 

@@ -47,7 +47,8 @@ transpose_xy(const T *__restrict__ in, T *__restrict__ out, int nx, int ny, int 
 // The two FP32 copies the forward sweeps stage from: the volume as it is
 // ([z][y][pitch]) and with x and y swapped ([z][x][pitch]), rows between zero
 // pads (sweep_pitch), so that the sweeps load quads of voxels without a test
-// of their single voxels, whatever the storage.
+// of their single voxels, whatever the storage.  A copy that no tile reads (a
+// single projection's rays mostly run along one axis) is null and not made.
 template <class VS>
 __global__ void __launch_bounds__(256)
 sweep_copies(const typename VS::T *__restrict__ in, float *__restrict__ wide,
@@ -67,10 +68,12 @@ sweep_copies(const typename VS::T *__restrict__ in, float *__restrict__ wide,
             float v = 0.0f;
             if ((unsigned)x < (unsigned)nx && (unsigned)y < (unsigned)ny)
                 v = VS::wide(VS::raw(in, ((size_t)sl * ny + y) * nx + x));
-            if ((unsigned)y < (unsigned)ny && x + kSweepPad < px)
+            if (wide && (unsigned)y < (unsigned)ny && x + kSweepPad < px)
                 wide[((size_t)sl * ny + y) * px + x + kSweepPad] = v;
             tile[j][lx] = v;
         }
+        if (!out)
+            continue;
         __syncthreads();
 #pragma unroll
         for (int j = ly; j < 32; j += 8) {
@@ -89,10 +92,12 @@ inline void launch_transpose_xy(const T *in, T *out, int nx, int ny, int n_slice
     hipLaunchKernelGGL((transpose_xy<T>), grid, dim3(256), 0, s, in, out, nx, ny, n_slices);
 }
 
-// FP32 words of the two copies of n_slices slices, and the copies made in `buf`.
-inline size_t sweep_words(int nx, int ny, size_t n_slices)
+// FP32 words of the copies of n_slices slices that a plan's tiles read (axes:
+// 1 x planes, the swapped copy; 2 y planes), and the copies made in `buf`.
+inline size_t sweep_words(int nx, int ny, size_t n_slices, int axes)
 {
-    return n_slices * ((size_t)ny * sweep_pitch(nx) + (size_t)nx * sweep_pitch(ny));
+    return n_slices * ((axes & 2 ? (size_t)ny * sweep_pitch(nx) : 0) +
+                       (axes & 1 ? (size_t)nx * sweep_pitch(ny) : 0));
 }
 
 struct SweepVolumes {
@@ -100,9 +105,12 @@ struct SweepVolumes {
 };
 
 inline SweepVolumes make_sweep_volumes(const void *vol, cbct_dtype t, float *buf, int nx, int ny,
-                                       int n_slices, hipStream_t s)
+                                       int n_slices, int axes, hipStream_t s)
 {
-    float *wide = buf, *out = buf + (size_t)n_slices * ny * sweep_pitch(nx);
+    if (!axes)
+        return {buf, buf};   // no tile meets the volume
+    float *wide = axes & 2 ? buf : nullptr;
+    float *out = axes & 1 ? buf + sweep_words(nx, ny, n_slices, axes & 2) : nullptr;
     const dim3 grid(((sweep_pitch(nx) + 31) / 32) * ((sweep_pitch(ny) + 31) / 32),
                     std::min(n_slices, 65535));
     if (t == CBCT_F32)
