@@ -32,8 +32,6 @@ namespace cbct {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxR = 8;       // rays per thread
-constexpr int kFewR = 4;       // where there are few tiles (see the plan)
 // Planes whose boxes are loaded ahead (two: 7.83 ms against 7.82, 11 registers more).
 constexpr int kPlanes = 1;
 // Rays whose LDS reads run ahead of the arithmetic.  With all eight rays' reads
@@ -50,29 +48,26 @@ static_assert(kBoxChunk == kThreads, "the box table is filled one plane per thre
 // LDS: two staging boxes, then the box table (one int4 per plane of a chunk)
 constexpr size_t kFwdLds = 2 * (size_t)kMaxRows * kQS * sizeof(float) + kBoxChunk * 16;
 
-// Sweep one tile.  R (rays per thread, 1..8) is uniform per tile; the per
+// Sweep one tile.  R (rays per thread) is a property of the plan; the per
 // ray arithmetic does not depend on it, so any launch shape gives the same
 // bits.  `lds` holds two boxes of kMaxRows x kQS floats and the box table.
 //
 // On plane p the box spans in-plane indices [qlo, qlo + qw) and z indices
 // [klo, klo + kw), from the corner rays' crossings widened by one voxel for
 // rounding; a wave stages four rows per load, a quad of voxels per lane.
-// tub: log2 of the tile width (6 or 5).  RC > 0 fixes R at compile time (the
-// plans' usual 8 rays per thread): the per-ray tests then vanish, which
-// matters because the sweep issues nearly as many scalar as vector
-// instructions and a SIMD takes one of each per four cycles.
+// tub: log2 of the tile width (6 or 5).  R: rays per thread, fixed at compile
+// time: the plans take 8, 4, 2 or 1, and a kernel with arrays of eight rays
+// for any of them spills 22 of its 72 registers, some reloads per plane.
 // v: the volume in FP32, vt: the same with x and y swapped ([nz][nx][ny]).  Tiles that
 // sweep x planes read their boxes from it, so a box row (fixed z, in-plane
 // index y) is contiguous; in the volume itself its voxels lie nx apart, a
 // cache line each (the clinical forward, an earlier build: 12.2 ms reading
 // them strided, 8.8 ms from the transposed copy).
-template <class SS, int RC = 0>
-__device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, int R_rt, int tub,
+template <class SS, int R>
+__device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, int tub,
                            const float *__restrict__ v, const float *__restrict__ vt,
                            typename SS::T *__restrict__ sino, float *lds)
 {
-    constexpr int NR = RC > 0 ? RC : kMaxR;
-    const int R = RC > 0 ? RC : R_rt;
     const int tid = threadIdx.x;
     // the wave index is uniform: the staging's slot tests below are scalar
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -81,10 +76,10 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
     const int ul = min(uc, T.nu_t - 1);
     const ColRec c = g.cols[(size_t)T.a * g.nu + T.u0 + ul];
 
-    float kb[NR], ks[NR], acc[NR];
+    float kb[R], ks[R], acc[R];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int vr = T.v0 + min(row0 + min(r, R - 1), T.nv_t - 1);
+    for (int r = 0; r < R; ++r) {
+        const int vr = T.v0 + min(row0 + r, T.nv_t - 1);
         const float vz = g.rows[vr].x;
         kb[r] = fmaf(c.t0, vz, g.Kb);
         ks[r] = c.tau * vz;
@@ -203,7 +198,7 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
             (int)(lds_addr(buf) + 4u * (uint32_t)((int)qf - cb.qlo)) - cb.klo * (4 * kQS);
         // ray r's arithmetic runs while the reads of the next kAhead rays are
         // in flight; the scheduling barriers keep that order
-        float wk[NR], v00[NR], v10[NR], v01[NR], v11[NR];
+        float wk[R], v00[R], v10[R], v01[R], v11[R];
         auto read = [&](int r) {
             // z index k of the ray on this plane: its weight is the
             // exact fraction of k, its row address one floor conversion
@@ -219,19 +214,16 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
         };
 #pragma unroll
         for (int r = 0; r < kAhead; ++r)
-            if (r < R)
-                read(r);
+            read(r);
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
+        for (int r = 0; r < R; ++r) {
             __builtin_amdgcn_sched_barrier(0);
-            if (r + kAhead < NR && r + kAhead < R)
+            if (r + kAhead < R)
                 read(r + kAhead);
             __builtin_amdgcn_sched_barrier(0);
-            if (r < R) {
-                const float lo = fmaf(wq, v10[r] - v00[r], v00[r]);
-                const float hi = fmaf(wq, v11[r] - v01[r], v01[r]);
-                acc[r] += fmaf(wk[r], hi - lo, lo);
-            }
+            const float lo = fmaf(wq, v10[r] - v00[r], v00[r]);
+            const float hi = fmaf(wq, v11[r] - v01[r], v01[r]);
+            acc[r] += fmaf(wk[r], hi - lo, lo);
         }
     };
     Box nb[kPlanes];
@@ -261,19 +253,19 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
         // eight registers throughout)
         int rb = row0;
         asm volatile("" : "+v"(rb));
-        float ds[NR];
+        float ds[R];
 #pragma unroll
-        for (int r = 0; r < NR; ++r)
+        for (int r = 0; r < R; ++r)
             ds[r] = g.rows[T.v0 + min(rb + r, T.nv_t - 1)].y;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
+        for (int r = 0; r < R; ++r) {
             ds[r] = ray_ds(c.dsf, c.n2, ds[r]);
             asm volatile("" : "+v"(ds[r]));
         }
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
+        for (int r = 0; r < R; ++r) {
             const int vr = row0 + r;
-            if (r < R && vr < T.nv_t)
+            if (vr < T.nv_t)
                 SS::st(sino, ((size_t)T.a * g.nv + T.v0 + vr) * g.nu + T.u0 + uc, acc[r] * ds[r]);
         }
     }
@@ -282,14 +274,14 @@ __device__ __forceinline__ void sweep_tile(const DevGeom &g, const TileRec &T, i
 struct SweepArgs {
     DevGeom g;
     const TileRec *tiles;
-    int R, tub;   // rays per thread, log2 of the tile width
+    int tub;   // log2 of the tile width
 };
 
 // Seven waves per SIMD (72 registers; the LDS of seven workgroups fits a CU).
 // The sweep is bound by VALU issue (5.2e9 wave instructions, the whole
 // of its 7.7 ms), so more waves only fill the gaps between dependent reads:
 // clinical forward 8.06 ms at five, 7.84 at six, 7.71 at seven.
-template <class SS, int RC>
+template <class SS, int R>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 7)))
 forward_sweep(SweepArgs A, const float *__restrict__ vol, const float *__restrict__ volt,
               typename SS::T *__restrict__ sino)
@@ -307,7 +299,7 @@ forward_sweep(SweepArgs A, const float *__restrict__ vol, const float *__restric
     const size_t nsino = (size_t)A.g.n_angles * A.g.nv * A.g.nu;
     const size_t nv = (size_t)A.g.nz * A.g.ny * sweep_pitch(A.g.nx);
     const size_t nt = (size_t)A.g.nz * A.g.nx * sweep_pitch(A.g.ny);
-    sweep_tile<SS, RC>(A.g, T, A.R, A.tub, vol + ch * nv, volt + ch * nt, sino + ch * nsino, lds);
+    sweep_tile<SS, R>(A.g, T, A.tub, vol + ch * nv, volt + ch * nt, sino + ch * nsino, lds);
 }
 
 // ---- batched forward: one launch over all (case, tile) items ----------------
@@ -344,14 +336,13 @@ forward_batch(BatchFwdArgs B)
     const TileRec T = C.tiles[item - B.first[cs]];
     if (T.nu_t == 0)
         return;
-    // cases with the usual rays per thread take the sweep specialised for it
-    // (a uniform branch; the bits do not depend on the variant)
-    if (C.R == kMaxR)
-        sweep_tile<SS, kMaxR>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
-    else if (C.R == kFewR)
-        sweep_tile<SS, kFewR>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
-    else
-        sweep_tile<SS>(C.g, T, C.R, C.tub, C.vol, C.volt, (typename SS::T *)C.sino, lds);
+    auto *sino = (typename SS::T *)C.sino;
+    switch (C.R) {   // uniform over the workgroup; the bits do not depend on it
+    case 8: sweep_tile<SS, 8>(C.g, T, C.tub, C.vol, C.volt, sino, lds); break;
+    case 4: sweep_tile<SS, 4>(C.g, T, C.tub, C.vol, C.volt, sino, lds); break;
+    case 2: sweep_tile<SS, 2>(C.g, T, C.tub, C.vol, C.volt, sino, lds); break;
+    default: sweep_tile<SS, 1>(C.g, T, C.tub, C.vol, C.volt, sino, lds); break;
+    }
 }
 
 }  // namespace
@@ -360,7 +351,7 @@ hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *
                                 cbct_dtype vt, void *sino, cbct_dtype st, int channels,
                                 hipStream_t s)
 {
-    SweepArgs A{g, p.tiles, p.R, p.TU == 32 ? 5 : 6};
+    SweepArgs A{g, p.tiles, p.TU == 32 ? 5 : 6};
     const size_t lds = kFwdLds;
     dim3 grid(p.n_tiles, channels), block(kThreads);
     // the volume with x and y swapped (and in FP32), in the library's device
@@ -374,12 +365,15 @@ hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *
         e = dispatch_storage(vt, st, [&](auto, auto ss) -> hipError_t {
             using SS = decltype(ss);
             auto *y = (typename SS::T *)sino;
-            if (p.R == kMaxR)
-                hipLaunchKernelGGL((forward_sweep<SS, kMaxR>), grid, block, lds, s, A, v.vol, v.volt, y);
-            else if (p.R == kFewR)
-                hipLaunchKernelGGL((forward_sweep<SS, kFewR>), grid, block, lds, s, A, v.vol, v.volt, y);
-            else
-                hipLaunchKernelGGL((forward_sweep<SS, 0>), grid, block, lds, s, A, v.vol, v.volt, y);
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, block, lds, s, A, v.vol, v.volt, y);
+            };
+            switch (p.R) {
+            case 8: launch(forward_sweep<SS, 8>); break;
+            case 4: launch(forward_sweep<SS, 4>); break;
+            case 2: launch(forward_sweep<SS, 2>); break;
+            default: launch(forward_sweep<SS, 1>); break;
+            }
             return hipGetLastError();
         });
     }
