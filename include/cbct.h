@@ -131,7 +131,9 @@ cbct_status cbct_geom_sizes(const cbct_geom *g, uint64_t *n_vox, uint64_t *n_sin
  * into the device buffer the library owns
  * (the one cbct_adjoint uses: the first call on a device, or a larger one,
  * allocates; calls on different streams are ordered on it): its tiles stage
- * their boxes from them.  Multichannel FP32 stacks pack
+ * their boxes from them.  Channels whose copies take more than 4 GiB together,
+ * or find no memory, run in several launches; one volume whose copies find no
+ * memory runs the one-thread-per-ray kernel.  Multichannel FP32 stacks pack
  * their channels there instead.
  */
 cbct_status cbct_forward(const cbct_geom *g, const void *vol, cbct_dtype vt,
@@ -145,7 +147,8 @@ cbct_status cbct_forward(const cbct_geom *g, const void *vol, cbct_dtype vt,
  * kernel with the same weights (slower).
  * The bricked kernel first writes the projections times each ray's length
  * per plane (FP32, C x n_angles*nv*nu values; for few bricks also up to eight
- * partial volumes of C x nx*ny*nz) into a device buffer the
+ * partial volumes of C x nx*ny*nz; above 4 GiB in several launches) into a
+ * device buffer the
  * library owns, one per device, kept until the process ends and grown when
  * a call needs more: the first call on a device, and any larger one,
  * allocates (so it must not be the one captured into a graph).  Calls on

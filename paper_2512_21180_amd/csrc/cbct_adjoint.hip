@@ -1064,9 +1064,9 @@ hipError_t launch_adjoint_mc(const cbct_geom *g, int C, const float *const *sino
     return e != hipSuccess ? e : r;
 }
 
-hipError_t launch_adjoint_brick(const DevGeom &g, const AdjPlan &p, const void *sino,
-                                cbct_dtype st, void *vol, cbct_dtype vt, int channels,
-                                hipStream_t s)
+static hipError_t gather_channels(const DevGeom &g, const AdjPlan &p, const void *sino,
+                                  cbct_dtype st, void *vol, cbct_dtype vt, int channels,
+                                  hipStream_t s)
 {
     BrickArgs A = brick_args(g, p);
     dim3 grid(8 * slots_per_xcd(A), channels, p.split), block(kThreads);
@@ -1097,6 +1097,28 @@ hipError_t launch_adjoint_brick(const DevGeom &g, const AdjPlan &p, const void *
         });
     const hipError_t r = scratch_release(s, lease);
     return e != hipSuccess ? e : r;
+}
+
+// Staged projections and partial volumes held at a time: stacks that take more
+// run in several launches.
+constexpr size_t kStageBytes = (size_t)4 << 30;
+
+hipError_t launch_adjoint_brick(const DevGeom &g, const AdjPlan &p, const void *sino,
+                                cbct_dtype st, void *vol, cbct_dtype vt, int channels,
+                                hipStream_t s)
+{
+    const size_t nvox = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.n_angles * g.nv * g.nu;
+    const size_t one = (nsino + part_words(p, nvox)) * sizeof(float);
+    const int most = (int)std::max<size_t>(1, std::min<size_t>(channels, kStageBytes / one));
+    for (int c0 = 0; c0 < channels; c0 += most) {
+        const hipError_t e =
+            gather_channels(g, p, (const char *)sino + c0 * nsino * storage_bytes(st), st,
+                            (char *)vol + c0 * nvox * storage_bytes(vt), vt,
+                            std::min(most, channels - c0), s);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_adjoint_batch(int n, const cbct_geom *const *gs, const void *const *sinos,

@@ -40,6 +40,11 @@ constexpr int kPlanes = 1;
 // clinical forward 9.6 ms; 8.11 one ray ahead, 8.13 two, 8.21 three, 8.35 four
 // (at five waves per SIMD).
 constexpr int kAhead = 1;
+// Volume copies made at a time: stacks and batches whose copies take more run in
+// several launches (each of half a billion voxels), as do those whose copies
+// find no memory; a single volume's copies that find none are not made, and
+// its rays summed one per thread instead.
+constexpr size_t kCopyBytes = (size_t)4 << 30;
 
 constexpr int kQS = 68;        // LDS row stride (floats): box rows are <= 64 wide
 constexpr int kMaxRows = 32;   // box rows (z) per plane
@@ -347,15 +352,14 @@ forward_batch(BatchFwdArgs B)
 
 }  // namespace
 
-hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *vol,
-                                cbct_dtype vt, void *sino, cbct_dtype st, int channels,
-                                hipStream_t s)
+// The sweep of `channels` channels, staged from copies in the library's device
+// buffer (in FP32, with x and y swapped for the tiles that sweep x planes).
+static hipError_t sweep_channels(const DevGeom &g, const FwdPlan &p, const void *vol, cbct_dtype vt,
+                                 void *sino, cbct_dtype st, int channels, hipStream_t s)
 {
     SweepArgs A{g, p.tiles, p.TU == 32 ? 5 : 6};
     const size_t lds = kFwdLds;
     dim3 grid(p.n_tiles, channels), block(kThreads);
-    // the volume with x and y swapped (and in FP32), in the library's device
-    // buffer, for the tiles that sweep x planes (and for 16-bit volumes)
     ScratchLease lease;
     hipError_t e = scratch_acquire(
         sweep_words(g.nx, g.ny, (size_t)g.nz * channels, p.axes) * sizeof(float), s, lease);
@@ -381,6 +385,33 @@ hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *
     return e != hipSuccess ? e : r;
 }
 
+hipError_t launch_forward_tiled(const DevGeom &g, const FwdPlan &p, const void *vol,
+                                cbct_dtype vt, void *sino, cbct_dtype st, int channels,
+                                hipStream_t s)
+{
+    const size_t nvox = (size_t)g.nx * g.ny * g.nz, nsino = (size_t)g.n_angles * g.nv * g.nu;
+    const size_t one = sweep_words(g.nx, g.ny, g.nz, p.axes) * sizeof(float);
+    int most = (int)std::max<size_t>(1, std::min<size_t>(channels, kCopyBytes / std::max<size_t>(one, 1)));
+    for (int c0 = 0; c0 < channels;) {
+        const int c = std::min(most, channels - c0);
+        const char *x = (const char *)vol + c0 * nvox * storage_bytes(vt);
+        char *y = (char *)sino + c0 * nsino * storage_bytes(st);
+        hipError_t e = sweep_channels(g, p, x, vt, y, st, c, s);
+        if (e == hipErrorOutOfMemory) {   // before any work was enqueued
+            (void)hipGetLastError();
+            if (c > 1) {
+                most = c / 2;
+                continue;
+            }
+            e = launch_forward_simple(g, x, vt, y, st, 1, s);
+        }
+        if (e != hipSuccess)
+            return e;
+        c0 += c;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_forward_batch(int n, const cbct_geom *const *gs, const void *const *vols,
                                 void *const *sinos, cbct_dtype vt, cbct_dtype st, hipStream_t s)
 {
@@ -400,8 +431,24 @@ hipError_t launch_forward_batch(int n, const cbct_geom *const *gs, const void *c
     B.first[n] = items;
     B.n_items = items;
     const int grid = (items + 7) / 8 * 8;
+    // fewer cases at a time, down to one
+    auto in_parts = [&]() -> hipError_t {
+        if (n == 1)
+            return launch_forward_tiled(gs[0]->dev, gs[0]->fwd, vols[0], vt, sinos[0], st, 1, s);
+        const int h = n / 2;
+        const hipError_t e = launch_forward_batch(h, gs, vols, sinos, vt, st, s);
+        return e != hipSuccess ? e
+                               : launch_forward_batch(n - h, gs + h, vols + h, sinos + h, vt, st, s);
+    };
+    if (total * sizeof(float) > kCopyBytes)
+        return in_parts();
     ScratchLease lease;
     hipError_t e = scratch_acquire(total * sizeof(float), s, lease);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        (void)scratch_release(s, lease);
+        return in_parts();
+    }
     if (e == hipSuccess) {
         for (int i = 0; i < n; ++i) {
             const DevGeom &d = gs[i]->dev;
