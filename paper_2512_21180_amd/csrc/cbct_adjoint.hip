@@ -53,6 +53,7 @@
 // clinical adjoint took 13.98 ms (now 12.70), the 64^3 one 220 us (150), four
 // channels of 128^3 x 180 x 256^2 6.0 ms (4.7).  Bound by VALU issue in the taps
 // where windows are tall, by the per-column set-up where runs are short.
+// SOLO kernels do take every angle by itself (see take_solo); the bits are the same.
 
 #include <hip/hip_runtime.h>
 
@@ -80,7 +81,7 @@ struct BrickArgs {
     int KV;                // voxels per lane along z (bricks 8 x 7 x 4 KV)
     int gw;                // panel windows staged at a time: 4, 2 or 1
     int area;              // LDS words of the windows
-    int split;             // ranges of angles gathered apart
+    int split, per;        // ranges of angles gathered apart, angles in each
     float rbias;           // 1 - adj_start_delta(nv)
     int plan_bk;           // layers of the plan's bricks (four channels take shorter ones)
 };
@@ -115,8 +116,7 @@ struct AngleEnt {
     float lmin, lmax;   // extreme source-panel scales of the brick's support
 };
 static_assert(sizeof(AngleEnt) == 32, "AngleEnt layout");
-constexpr int kListAngles = 32;   // angles listed at a time
-constexpr int kGroup = 4;         // angles whose column ranges are found at a time
+constexpr int kListAngles = kAdjListAngles, kGroup = kAdjGroup;
 
 __device__ inline AngleEnt uniform_ent(const AngleEnt &e)
 {
@@ -330,7 +330,7 @@ __device__ inline uint2 column_ranges(const DevGeom &g, const AngleEnt &e, const
 __device__ inline void stage_columns(const DevGeom &g, const AngleEnt &e, int lane, float4 *cr)
 {
     const int U0 = (int)(e.u01 & 0xffffu), U1 = (int)(e.u01 >> 16);
-    for (int u = U0 + lane; u <= U1; u += 64) {
+    for (int u = U0 + lane; u <= U1; u += 64) {   // lane: first column, from U0
         const ColRec col = g.cols[(size_t)e.a * g.nu + u];
         cr[u - U0] = make_float4(col.pb, col.ps, col.t0, col.tau);
     }
@@ -421,7 +421,12 @@ __device__ __forceinline__ void stage_tall(const DevGeom &g, __amdgpu_buffer_rsr
     }
 }
 
-// Gather one brick (index b): bricks hold kAdjBI x kAdjBJ x 4 KV output
+// Brick coordinates.
+struct BrickAt {
+    int bx, by, bz;
+};
+
+// Gather one brick: bricks hold kAdjBI x kAdjBJ x 4 KV output
 // voxels.  Lane roles (wave w owns the KV voxel layers from 4 KV (brick z) +
 // KV w up): on x planes lane l takes plane i0 + l % 8 and in-plane segment
 // j0 - 1 + l / 8 (eight segments serve the seven output rows j0 .. j0 + 6);
@@ -431,26 +436,25 @@ __device__ __forceinline__ void stage_tall(const DevGeom &g, __amdgpu_buffer_rsr
 // the one below, on each axis) are added in a fixed order through LDS.
 // Only the given range of the angles is gathered; where there are several,
 // `part` receives its sums in FP32.
-// `lds` holds the panel window, column-major ([W][HS], HS = 2 mod 4, which
-// suits the gather's reads), and the column table; then the exchange.
-template <class VS, int KV, bool TALL, int C = 1>
-__device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int range,
+// `lds` holds the column table and the panel window, column-major ([W][HS],
+// HS = 2 mod 4, which suits the gather's reads); then the exchange.
+template <class VS, int KV, bool TALL, int C = 1, bool SOLO = false>
+__device__ __forceinline__ void gather_brick(const BrickArgs &A, BrickAt at, int range,
                                              const float *ws, typename VS::T *const (&vol)[C],
                                              float *part, float *lds)
 {
     constexpr int kBK = 4 * KV;
     constexpr int kSB = kStageRows;
     const DevGeom &g = A.g;
-    const int HS = A.HS, cols = A.W * HS * C;           // words before a window's column records
-    const int win = cols + 4 * A.W;                     // words of a window with them
+    const int HS = A.HS, recs = 4 * A.W;                // words of the column records before a window
+    const int win = recs + A.W * HS * C;                // words of a window with them
     uint2 *ranges = (uint2 *)(lds + A.area);            // [kGroup][64]
     AngleEnt *list = (AngleEnt *)(ranges + kGroup * 64);
     int *listed = (int *)(list + kListAngles);
 
     // this range of the angles
-    const int per = (g.n_angles + A.split - 1) / A.split;
-    const int a_lo = range * per, a_hi = min(a_lo + per, g.n_angles);
-    const int bx = b % A.nbx, by = (b / A.nbx) % A.nby, bz = b / (A.nbx * A.nby);
+    const int a_lo = range * A.per, a_hi = min(a_lo + A.per, g.n_angles);
+    const int bx = at.bx, by = at.by, bz = at.bz;
 
     // the wave index is uniform (scalar registers for its row and layer indices)
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -543,8 +547,8 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
         }
     };
 
-    // One angle's gather from its staged window.
-    auto gather = [&](const AngleEnt &e, uint2 range, const float *yt) {
+    // One angle's gather from its staged window; `columns` gives the lane's ranges.
+    auto gather = [&](const AngleEnt &e, auto columns, const float *yt) {
         const int U0 = (int)(e.u01 & 0xffffu), V0 = e.V0;
         const int V1 = V0 + (int)(e.hn & 0xffffu) - 1, NT = (int)(e.hn >> 16);
         const int VS1 = max(V1 - NT + 1, V0);
@@ -560,8 +564,8 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
             return;
         // compile-time tap count (NT rounded up to a supported count; extra
         // taps read zero weight)
-        const GatherIn in{g, e.x_lo, e.x_hi, yt, (const float4 *)(yt + cols), HS, U0, V0, VS1,
-                          k0, {pl[0], pl[1]}, {sg[0], sg[1]}, range, inv_rvs, A.rbias, NT >> 3};
+        const GatherIn in{g, e.x_lo, e.x_hi, yt, (const float4 *)(yt - recs), HS, U0, V0, VS1,
+                          k0, {pl[0], pl[1]}, {sg[0], sg[1]}, columns(), inv_rvs, A.rbias, NT >> 3};
         if constexpr (C > 1) {   // at most 8 (see kMaxTapsMc)
             switch (NT) {
             case 4: gather_angle<4, KV, C>(in, lo, hi); break;
@@ -595,58 +599,82 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
         }
     };
 
-    for (int base = a_lo; base < a_hi; base += kListAngles) {
+    // One angle's entry: columns and row taps from the table, rows from the
+    // extreme source-panel scales (positive) at the support's lowest and highest
+    // z; false where the window misses the panel.
+    auto entry = [&](int a, AngleEnt &e) {
+        const BrickWin bw = wcol[(size_t)a * wstep];
+        const AngRec ar = g.angs[a];
+        const int U0 = (int)(bw.u01 & 0xffffu);
+        const int U1 = min((int)(bw.u01 >> 16), U0 + A.W - 1);
+        auto window_rows = [&](float za, float zb, int &v0, int &v1) {
+            const float vmin =
+                fmaf(fminf(bw.lmin * za, bw.lmax * za) - g.off_v, inv_dv, g.cv);
+            const float vmax =
+                fmaf(fmaxf(bw.lmin * zb, bw.lmax * zb) - g.off_v, inv_dv, g.cv);
+            v0 = max((int)floorf(vmin) - 2, 0);
+            v1 = min(min((int)ceilf(vmax) + 2, g.nv - 1), v0 + A.H - 1);
+        };
+        int V0, V1;
+        window_rows(zs0, zs1, V0, V1);
+        const bool seen = U0 <= U1 && V0 <= V1;
+        if constexpr (C == 4) {
+            // A run starts at most NT - 1 rows below its window's last
+            // row, and from another start its weights round
+            // differently: for the bits of a single call the starts are
+            // bounded by the window P0 .. P1 of the plan's brick that
+            // holds this one.  So this window keeps the rows of P0 .. P1
+            // that a run may take from its own start (at most one row
+            // above the highest crossing of z index k - 1) or from the
+            // bounded one.
+            const int p0 = kz0 / A.plan_bk * A.plan_bk;
+            const int p1 = min(p0 + A.plan_bk, g.nz) - 1;
+            int P0, P1;
+            window_rows(support_z(p0, -1), support_z(p1, 1), P0, P1);
+            const float zc = zs1 - 2.0f * g.vz;
+            const float vc =
+                fmaf(fmaxf(bw.lmin * zc, bw.lmax * zc) - g.off_v, inv_dv, g.cv);
+            V0 = min(V0, max(P1 - bw.nt + 1, P0));
+            V1 = min(P1, max(V1, (int)floorf(vc) + 1 + bw.nt));
+        }
+        e = AngleEnt{a, (uint32_t)U0 | (uint32_t)U1 << 16, V0,
+                     (uint32_t)(V1 - V0 + 1) | (uint32_t)bw.nt << 16, ar.x_lo, ar.x_hi, bw.lmin,
+                     bw.lmax};
+        return seen;
+    };
+
+    if constexpr (SOLO) {
+        // ---- one angle after another, each wave finding its column ranges: the
+        // window and its records alone in LDS
+        __syncthreads();   // the previous work item's readers are done
+        for (int a = a_lo; a < a_hi; ++a) {
+            AngleEnt e;
+            if (!__builtin_amdgcn_readfirstlane((int)entry(a, e)))
+                continue;
+            e = uniform_ent(e);
+            __syncthreads();   // the previous angle's readers are done
+            // wave 0's column records are loaded with its rows, stored after them
+            const int U0 = (int)(e.u01 & 0xffffu), Wc = (int)(e.u01 >> 16) - U0 + 1;
+            float4 *cr = (float4 *)lds;
+            ColRec col;
+            if (w == 0)
+                col = g.cols[(size_t)e.a * g.nu + U0 + min(lane, Wc - 1)];
+            stage_window(e, lds + recs);
+            if (w == 0) {
+                cr[min(lane, Wc - 1)] = make_float4(col.pb, col.ps, col.t0, col.tau);
+                stage_columns(g, e, lane + 64, cr);
+            }
+            __syncthreads();
+            gather(e, [&] { return column_ranges(g, e, pl, sg, inv_du, cr); }, lds + recs);
+        }
+    }
+    for (int base = SOLO ? a_hi : a_lo; base < a_hi; base += kListAngles) {
         __syncthreads();   // the readers of the previous list (or work item) are done
-        // ---- the next 32 angles at which the window meets the panel: columns
-        // and row taps from the table, rows from the extreme source-panel
-        // scales (positive) at the support's lowest and highest z
+        // ---- the next 32 angles at which the window meets the panel
         if (w == 0) {
             AngleEnt e{};
-            bool seen = false;
-            e.a = base + lane;
-            if (lane < kListAngles && e.a < a_hi) {
-                const BrickWin bw = wcol[(size_t)e.a * wstep];
-                const AngRec ar = g.angs[e.a];
-                const int U0 = (int)(bw.u01 & 0xffffu);
-                const int U1 = min((int)(bw.u01 >> 16), U0 + A.W - 1);
-                auto window_rows = [&](float za, float zb, int &v0, int &v1) {
-                    const float vmin =
-                        fmaf(fminf(bw.lmin * za, bw.lmax * za) - g.off_v, inv_dv, g.cv);
-                    const float vmax =
-                        fmaf(fmaxf(bw.lmin * zb, bw.lmax * zb) - g.off_v, inv_dv, g.cv);
-                    v0 = max((int)floorf(vmin) - 2, 0);
-                    v1 = min(min((int)ceilf(vmax) + 2, g.nv - 1), v0 + A.H - 1);
-                };
-                int V0, V1;
-                window_rows(zs0, zs1, V0, V1);
-                seen = U0 <= U1 && V0 <= V1;
-                if constexpr (C == 4) {
-                    // A run starts at most NT - 1 rows below its window's last
-                    // row, and from another start its weights round
-                    // differently: for the bits of a single call the starts are
-                    // bounded by the window P0 .. P1 of the plan's brick that
-                    // holds this one.  So this window keeps the rows of P0 .. P1
-                    // that a run may take from its own start (at most one row
-                    // above the highest crossing of z index k - 1) or from the
-                    // bounded one.
-                    const int p0 = kz0 / A.plan_bk * A.plan_bk;
-                    const int p1 = min(p0 + A.plan_bk, g.nz) - 1;
-                    int P0, P1;
-                    window_rows(support_z(p0, -1), support_z(p1, 1), P0, P1);
-                    const float zc = zs1 - 2.0f * g.vz;
-                    const float vc =
-                        fmaf(fmaxf(bw.lmin * zc, bw.lmax * zc) - g.off_v, inv_dv, g.cv);
-                    V0 = min(V0, max(P1 - bw.nt + 1, P0));
-                    V1 = min(P1, max(V1, (int)floorf(vc) + 1 + bw.nt));
-                }
-                e.u01 = (uint32_t)U0 | (uint32_t)U1 << 16;
-                e.V0 = V0;
-                e.hn = (uint32_t)(V1 - V0 + 1) | (uint32_t)bw.nt << 16;
-                e.x_lo = ar.x_lo;
-                e.x_hi = ar.x_hi;
-                e.lmin = bw.lmin;
-                e.lmax = bw.lmax;
-            }
+            const int a = base + lane;
+            const bool seen = lane < kListAngles && a < a_hi && entry(a, e);
             const uint64_t m = __ballot(seen);
             if (seen)
                 list[__builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)] = e;
@@ -666,7 +694,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
                 __syncthreads();   // the previous group's readers are done
             if (w < m) {
                 const AngleEnt e = uniform_ent(list[i0 + w]);
-                float4 *cr = (float4 *)(all ? lds + w * win + cols : lds + w * 4 * A.W);
+                float4 *cr = (float4 *)(lds + w * (all ? win : recs));
                 stage_columns(g, e, lane, cr);
                 if (!all) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -676,13 +704,13 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
             }
             if (all) {
                 for (int i = 0; i < m; ++i)
-                    stage_window(uniform_ent(list[i0 + i]), lds + i * win);
+                    stage_window(uniform_ent(list[i0 + i]), lds + i * win + recs);
                 if (w < m) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     ranges[w * 64 + lane] =
                         column_ranges(g, uniform_ent(list[i0 + w]), pl, sg, inv_du,
-                                      (const float4 *)(lds + w * win + cols));
+                                      (const float4 *)(lds + w * win));
                 }
             }
             for (int i = 0; i < m; i += A.gw) {
@@ -691,16 +719,16 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
                     __syncthreads();   // the windows' readers, or the ranges', are done
                     for (int j = 0; j < mi; ++j) {
                         const AngleEnt e = uniform_ent(list[i0 + i + j]);
-                        float *yt = lds + j * win;
+                        float *yt = lds + j * win + recs;
                         stage_window(e, yt);
                         if (w == j)
-                            stage_columns(g, e, lane, (float4 *)(yt + cols));
+                            stage_columns(g, e, lane, (float4 *)(yt - recs));
                     }
                 }
                 __syncthreads();
                 for (int j = 0; j < mi; ++j)
-                    gather(uniform_ent(list[i0 + i + j]), ranges[(i + j) * 64 + lane],
-                           lds + j * win);
+                    gather(uniform_ent(list[i0 + i + j]), [&] { return ranges[(i + j) * 64 + lane]; },
+                           lds + j * win + recs);
             }
         }
     }
@@ -751,26 +779,18 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, int b, int rang
 // Rows past the last multiple of eight are dealt out by brick columns, so no
 // XCD has a row more than another: with whole rows 10 rows (64^3) gave two XCDs
 // twice the others' work, 19 rows (128^3) three XCDs half as much again.
-// Slot li of XCD xc -> brick index, or -1 for the padding slots.
-__device__ inline int brick_of_slot(const BrickArgs &A, int xc, int li)
+// The brick of slot li of XCD xc; bx = -1 for the padding slots.
+__device__ inline BrickAt brick_of_slot(const BrickArgs &A, int xc, int li)
 {
-    const int plane = A.nbx * A.nbz, turns = A.nby / 8;
-    int bx, by, bz;
-    if (li < plane * turns) {
-        by = xc + 8 * (li / plane);
-        bz = (li % plane) / A.nbx;
-        bx = li % A.nbx;
-    } else {
-        const int columns = (A.nby % 8) * A.nbx, each = (columns + 7) / 8;
-        li -= plane * turns;
-        const int c = xc + 8 * (li % each);
-        if (c >= columns)
-            return -1;
-        by = 8 * turns + c / A.nbx;
-        bx = c % A.nbx;
-        bz = li / each;
+    const int plane = A.nbx * A.nbz, whole = plane * (A.nby / 8);
+    if (li < whole) {
+        const int row = li / plane, rest = li - row * plane, bz = rest / A.nbx;
+        return {rest - bz * A.nbx, xc + 8 * row, bz};
     }
-    return (bz * A.nby + by) * A.nbx + bx;
+    const int columns = (A.nby & 7) * A.nbx, each = (columns + 7) / 8;
+    li -= whole;
+    const int bz = li / each, c = xc + 8 * (li - bz * each), row = c / A.nbx;
+    return {c < columns ? c - row * A.nbx : -1, (A.nby & ~7) + row, bz};
 }
 
 // Slots per XCD of one case (padded so that every XCD has the same count).
@@ -779,22 +799,22 @@ __host__ __device__ inline int slots_per_xcd(const BrickArgs &A)
     return A.nbz * (A.nbx * (A.nby / 8) + ((A.nby % 8) * A.nbx + 7) / 8);
 }
 
-template <class VS, int KV, bool TALL>
+template <class VS, int KV, bool TALL, bool SOLO>
 __global__ void __launch_bounds__(kThreads, 4)
 adjoint_brick(BrickArgs A, const float *__restrict__ ws, typename VS::T *__restrict__ vol,
               float *__restrict__ part)
 {
     extern __shared__ float lds[];
-    const int b = brick_of_slot(A, blockIdx.x & 7, blockIdx.x >> 3);
-    if (b < 0)
+    const BrickAt b = brick_of_slot(A, blockIdx.x & 7, blockIdx.x >> 3);
+    if (b.bx < 0)
         return;
     const int ch = blockIdx.y;
     const size_t nvox = (size_t)A.g.nx * A.g.ny * A.g.nz;
     const size_t nsino = (size_t)A.g.n_angles * A.g.nv * A.g.nu;
     typename VS::T *const out[1] = {vol + ch * nvox};
     const size_t at = ((size_t)blockIdx.z * gridDim.y + ch) * nvox;
-    gather_brick<VS, KV, TALL>(A, b, blockIdx.z, ws + ch * nsino, out, part ? part + at : nullptr,
-                               lds);
+    gather_brick<VS, KV, TALL, 1, SOLO>(A, b, blockIdx.z, ws + ch * nsino, out,
+                                        part ? part + at : nullptr, lds);
 }
 
 // The ranges' volumes added in order.
@@ -835,8 +855,8 @@ __global__ void __launch_bounds__(kThreads, 3)
 adjoint_mc(McAdjArgs<C> B)
 {
     extern __shared__ float lds[];
-    const int b = brick_of_slot(B.A, blockIdx.x & 7, blockIdx.x >> 3);
-    if (b < 0)
+    const BrickAt b = brick_of_slot(B.A, blockIdx.x & 7, blockIdx.x >> 3);
+    if (b.bx < 0)
         return;
     gather_brick<F32, KV, false, C>(B.A, b, 0, B.ws, B.vol, nullptr, lds);
 }
@@ -903,7 +923,7 @@ struct BatchAdjArgs {
     AdjCase c[kMaxBatch];
 };
 
-template <class VS>
+template <class VS, bool SOLO>
 __global__ void __launch_bounds__(kThreads, 4)
 adjoint_batch(BatchAdjArgs B)
 {
@@ -916,35 +936,34 @@ adjoint_batch(BatchAdjArgs B)
         ++cs;
     const AdjCase &C = B.c[cs];
     const int slots = slots_per_xcd(C.A), range = (li - B.first[cs]) / slots;
-    const int b = brick_of_slot(C.A, xc, (li - B.first[cs]) % slots);
-    if (b < 0)
+    const BrickAt b = brick_of_slot(C.A, xc, li - B.first[cs] - range * slots);
+    if (b.bx < 0)
         return;
     const size_t nvox = (size_t)C.A.g.nx * C.A.g.ny * C.A.g.nz;
     float *part = C.part ? C.part + range * nvox : nullptr;
     typename VS::T *const vs[1] = {(typename VS::T *)C.vol};
     switch (C.A.KV) {   // uniform over the workgroup
-    case 4: gather_brick<VS, 4, false>(C.A, b, range, C.ws, vs, part, lds); break;
-    case 2: gather_brick<VS, 2, false>(C.A, b, range, C.ws, vs, part, lds); break;
-    default: gather_brick<VS, 1, false>(C.A, b, range, C.ws, vs, part, lds); break;
+    case 4: gather_brick<VS, 4, false, 1, SOLO>(C.A, b, range, C.ws, vs, part, lds); break;
+    case 2: gather_brick<VS, 2, false, 1, SOLO>(C.A, b, range, C.ws, vs, part, lds); break;
+    default: gather_brick<VS, 1, false, 1, SOLO>(C.A, b, range, C.ws, vs, part, lds); break;
     }
 }
 
 }  // namespace
 
-// Window columns, rounded up to even: with the column stride 2 mod 4 words
-// the column records behind a window are 16-byte aligned.
+// Window columns, rounded up to even (adj_window_words).
 static int even_width(const AdjPlan &p) { return p.W + (p.W & 1); }
 
 // Words of one panel window of C channels with its column records.
 static size_t window_words(const AdjPlan &p, int C)
 {
-    return (size_t)even_width(p) * ((size_t)p.WS * C + 4);
+    return adj_window_words(p.W, p.WS, C);
 }
 
-// Four workgroups share a CU up to this many words each (40 KB, less the list
-// and ranges): with that many windows at a time a group of angles takes two
-// barriers and one round trip to memory instead of eight and four.
-constexpr size_t kShareWords = 40 * 256 - (kGroup * 64 * 2 + kListAngles * 8 + 4);
+// With as many windows at a time as a workgroup's share of the LDS holds, a
+// group of angles takes two barriers and one round trip to memory instead of
+// eight and four.
+constexpr size_t kShareWords = kAdjShareWords;
 
 static int windows_at_a_time(const AdjPlan &p, int C)
 {
@@ -960,23 +979,41 @@ static size_t window_area(const AdjPlan &p, int C)
     return std::max(n * window_words(p, C), records);
 }
 
-static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p, int C = 1)
+static BrickArgs brick_args(const DevGeom &g, const AdjPlan &p, int C = 1, bool solo = false)
 {
     const int bk = 4 * p.KV;
-    return BrickArgs{g, p.wins, even_width(p), p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
+    return BrickArgs{g, p.wins, solo ? p.W : even_width(p), p.H, p.WS, (g.nx + kAdjBI - 1) / kAdjBI,
                      (g.ny + kAdjBJ - 1) / kAdjBJ, (g.nz + bk - 1) / bk, p.KV,   // WS: column stride
-                     windows_at_a_time(p, C), (int)window_area(p, C), p.split, 1.0f - adj_start_delta(g.nv),
+                     windows_at_a_time(p, C), (int)window_area(p, C), p.split,
+                     (g.n_angles + p.split - 1) / p.split, 1.0f - adj_start_delta(g.nv),
                      bk};
 }
 
 // The windows, the column ranges and the list of angles, or the final exchange
 // (four shares per lane and voxel layer, four waves) if that is larger.
-static size_t brick_lds(const AdjPlan &p, int C = 1)
+static size_t brick_lds(const AdjPlan &p, int C = 1, bool solo = false)
 {
-    const size_t gather = window_area(p, C) + kGroup * 64 * 2 +
-                          kListAngles * sizeof(AngleEnt) / sizeof(float) + 4;
+    static_assert(sizeof(AngleEnt) == 8 * sizeof(float), "kAdjSideWords counts eight words");
+    const size_t gather =
+        solo ? (size_t)p.W * (p.WS + 4) : window_area(p, C) + kAdjSideWords;
     const size_t exchange = (size_t)4 * 4 * 64 * p.KV;
     return std::max(gather, exchange) * sizeof(float);
+}
+
+// Workgroups of so much LDS that a CU holds (160 KB, given out in 1280 bytes).
+static size_t per_cu(size_t bytes) { return 128 / ((bytes + 1279) / 1280); }
+
+// One angle after another, without the list and the ranges in LDS: where their
+// 3 KB would cost a CU one of its (at most four) workgroups, and for fewer
+// angles than a group.  Windows of 38 to 40 KB: 182 x 156 x 113 x 180 angles of
+// 410 x 330, 3.00 ms with three workgroups and groups of angles, 2.82 with four
+// and one by one; shorter bricks with four and groups 3.23.  One angle of
+// 512 x 512 into 256^3: 105 us in a group, 95 alone; four angles 209 and 213.
+static bool take_solo(const AdjPlan &p, int n_angles)
+{
+    const size_t grouped = std::min<size_t>(per_cu(brick_lds(p)), 4);
+    const size_t solo = std::min<size_t>(per_cu(brick_lds(p, 1, true)), 4);
+    return solo > grouped || n_angles < kGroup;
 }
 
 // Words of the ranges' volumes of n voxels.
@@ -1068,7 +1105,8 @@ static hipError_t gather_channels(const DevGeom &g, const AdjPlan &p, const void
                                   cbct_dtype st, void *vol, cbct_dtype vt, int channels,
                                   hipStream_t s)
 {
-    BrickArgs A = brick_args(g, p);
+    const bool solo = take_solo(p, g.n_angles);
+    BrickArgs A = brick_args(g, p, 1, solo);
     dim3 grid(8 * slots_per_xcd(A), channels, p.split), block(kThreads);
     const size_t nsino = (size_t)g.n_angles * g.nv * g.nu * channels;
     const size_t nvox = (size_t)g.nx * g.ny * g.nz * channels;
@@ -1079,18 +1117,21 @@ static hipError_t gather_channels(const DevGeom &g, const AdjPlan &p, const void
     if (e == hipSuccess)
         e = dispatch_storage(vt, st, [&](auto vs, auto) -> hipError_t {
             using VS = decltype(vs);
-            const size_t lds = brick_lds(p);
+            const size_t lds = brick_lds(p, 1, solo);
             const float *w = (const float *)lease.ptr;
             float *part = p.split > 1 ? (float *)lease.ptr + nsino : nullptr;
             auto *x = (typename VS::T *)vol;
+            auto launch = [&](auto one, auto grouped) {
+                hipLaunchKernelGGL(solo ? one : grouped, grid, block, lds, s, A, w, x, part);
+            };
             if (adj_tall(p.KV, p.WS))
-                hipLaunchKernelGGL((adjoint_brick<VS, 4, true>), grid, block, lds, s, A, w, x, part);
+                launch(adjoint_brick<VS, 4, true, true>, adjoint_brick<VS, 4, true, false>);
             else if (p.KV == 4)
-                hipLaunchKernelGGL((adjoint_brick<VS, 4, false>), grid, block, lds, s, A, w, x, part);
+                launch(adjoint_brick<VS, 4, false, true>, adjoint_brick<VS, 4, false, false>);
             else if (p.KV == 2)
-                hipLaunchKernelGGL((adjoint_brick<VS, 2, false>), grid, block, lds, s, A, w, x, part);
+                launch(adjoint_brick<VS, 2, false, true>, adjoint_brick<VS, 2, false, false>);
             else
-                hipLaunchKernelGGL((adjoint_brick<VS, 1, false>), grid, block, lds, s, A, w, x, part);
+                launch(adjoint_brick<VS, 1, false, true>, adjoint_brick<VS, 1, false, false>);
             if (part)
                 launch_add_ranges<VS>(nvox, p.split, part, x, s);
             return hipGetLastError();
@@ -1129,12 +1170,15 @@ hipError_t launch_adjoint_batch(int n, const cbct_geom *const *gs, const void *c
     size_t lds = 0, total = 0;
     int items = 0;
     size_t off[kMaxBatch], parts[kMaxBatch];
+    bool solo = false;
+    for (int i = 0; i < n; ++i)
+        solo = solo || take_solo(gs[i]->adj, gs[i]->dev.n_angles);
     for (int i = 0; i < n; ++i) {
         const cbct_geom *g = gs[i];
         B.first[i] = items;
-        B.c[i] = AdjCase{brick_args(g->dev, g->adj), nullptr, vols[i], nullptr};
+        B.c[i] = AdjCase{brick_args(g->dev, g->adj, 1, solo), nullptr, vols[i], nullptr};
         items += slots_per_xcd(B.c[i].A) * g->adj.split;
-        lds = std::max(lds, brick_lds(g->adj));
+        lds = std::max(lds, brick_lds(g->adj, 1, solo));
         off[i] = total;
         total += (size_t)g->dev.n_angles * g->dev.nv * g->dev.nu;
         parts[i] = total;
@@ -1154,7 +1198,10 @@ hipError_t launch_adjoint_batch(int n, const cbct_geom *const *gs, const void *c
     if (e == hipSuccess)
         e = dispatch_storage(vt, st, [&](auto vs, auto) -> hipError_t {
             using VS = decltype(vs);
-            hipLaunchKernelGGL((adjoint_batch<VS>), dim3(grid), dim3(kThreads), lds, s, B);
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, B);
+            };
+            solo ? launch(adjoint_batch<VS, true>) : launch(adjoint_batch<VS, false>);
             for (int i = 0; i < n; ++i)
                 if (B.c[i].part)
                     launch_add_ranges<VS>((size_t)B.c[i].A.g.nx * B.c[i].A.g.ny * B.c[i].A.g.nz,

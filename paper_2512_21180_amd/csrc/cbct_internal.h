@@ -98,6 +98,20 @@ __host__ __device__ inline int adj_taps_rounded(int nt)
     return (nt + 7) & ~7;
 }
 
+// LDS words of an adjoint workgroup that gathers angles in groups: a panel window
+// of C channels and its column records (columns rounded up to even: with the
+// column stride 2 mod 4 words the next window's records are 16-byte aligned),
+// and beside the windows the column ranges of a group and the list of angles.
+constexpr int kAdjGroup = 4;         // angles whose column ranges are found at a time
+constexpr int kAdjListAngles = 32;   // angles listed at a time
+__host__ __device__ inline size_t adj_window_words(int W, int WS, int C)
+{
+    return (size_t)(W + (W & 1)) * ((size_t)WS * C + 4);
+}
+constexpr size_t kAdjSideWords = kAdjGroup * 64 * 2 + kAdjListAngles * 8 + 4;
+// Four workgroups share a CU up to this many words of windows each.
+constexpr size_t kAdjShareWords = 40 * 256 - kAdjSideWords;
+
 // The adjoint's row runs start at floor(v_c + 1 - delta), v_c the row where a
 // ray crosses a voxel's lower z support: delta exceeds the FP32 rounding of
 // v_c (a few units of the last place of a row index up to nv) several

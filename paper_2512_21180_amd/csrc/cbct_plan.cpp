@@ -38,7 +38,7 @@ namespace {
 constexpr int kMaxBoxQ = 64;      // staged box: one 64-lane row per z index
 constexpr int kMaxBoxK = 32;      // and at most 32 rows
 constexpr int kBI = kAdjBI, kBJ = kAdjBJ;
-constexpr size_t kAdjLdsShare = 40 * 1024;    // four workgroups per CU
+constexpr size_t kAdjLdsShare = 40 * 1024;    // window and records: four workgroups per CU
 constexpr size_t kAdjLdsBudget = 64 * 1024;
 constexpr long kMinBricks = 2 * 256;          // two bricks per CU
 constexpr int kMaxTaps = 128;      // row taps per voxel and column in the adjoint
