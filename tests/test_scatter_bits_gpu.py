@@ -44,8 +44,8 @@ def _captured(torch, cbct, geo, rho, X, rec, ref):
         yield out
 
 
-# one chunk; chunks of records with a remainder; more chunks than a phase has records
-@pytest.mark.parametrize("nu,nv,n", [(9, 7, 20), (17, 33, 45), (33, 17, 300), (8, 8, 31)])
+# one record; one chunk; chunks of records with a remainder; more chunks than a phase has records
+@pytest.mark.parametrize("nu,nv,n", [(128, 120, 1), (9, 7, 20), (17, 33, 45), (33, 17, 300), (8, 8, 31)])
 def test_routes_same_bits(dev, nu, nv, n):
     torch, cbct = dev
     print(f"[scatter] bits {nu}x{nv}, {n} records", flush=True)
