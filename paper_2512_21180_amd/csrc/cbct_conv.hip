@@ -53,6 +53,12 @@ __device__ inline uint32_t pk_bf(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf2));
 }
 
+// Four channels of a channel-last array of which only bf16 alignment is known
+// (the hardware takes eight bytes at any address, the compiler has to be told).
+struct __attribute__((packed, aligned(2))) Ch4 {
+    uint32_t x, y;
+};
+
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 struct PtrList {
@@ -106,7 +112,7 @@ struct ConvArgs {
 // (kRows + 2 rows x 66 positions x 16 channels per plane) rolls through a
 // ring of four planes in LDS: while plane z is computed from the planes
 // z - 1, z, z + 1, the loads of plane z + 2 are in flight and land in the
-// slot plane z - 2 held; one barrier per plane.  Each MFMA's A operand is
+// slot plane z - 2 held; one barrier per plane.  Each MFMA's B operand is
 // one 16-byte LDS read per lane (channels 0-7 and 8-15 in separate halves,
 // so the 16 lanes of a group read consecutive words).  The weights are read
 // once per workgroup straight into registers (the transposed kernel of the
@@ -233,14 +239,14 @@ k_conv3(ConvArgs A)
         const bool more = z + 1 < z1;   // uniform: the next plane needs z + 2
         // the epilogue's mask values, loaded ahead of the halo prefetch so
         // that waiting for them does not wait for it
-        uint2 mk[kBX / 16];
+        Ch4 mk[kBX / 16];
         if (MASK && row_live) {
 #pragma unroll
             for (int tx = 0; tx < kBX / 16; ++tx) {
                 const int xo = x0 + 16 * tx + m;
-                mk[tx] = xo < A.nx ? *reinterpret_cast<const uint2 *>(
+                mk[tx] = xo < A.nx ? *reinterpret_cast<const Ch4 *>(
                                          A.mask + (((size_t)z * A.ny + y) * A.nx + xo) * 16 + c0)
-                                   : make_uint2(0u, 0u);
+                                   : Ch4{0u, 0u};
             }
         }
         if (more)
@@ -304,8 +310,8 @@ k_conv3(ConvArgs A)
                         v[i] = v[i] > 0.0f ? v[i] : A.slope * v[i];
                 }
                 if (A.y_cl)
-                    *reinterpret_cast<uint2 *>(A.y_cl + pos * 16 + c0) =
-                        make_uint2(pk_bf(v[0], v[1]), pk_bf(v[2], v[3]));
+                    *reinterpret_cast<Ch4 *>(A.y_cl + pos * 16 + c0) =
+                        Ch4{pk_bf(v[0], v[1]), pk_bf(v[2], v[3])};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if (c0 + i < A.n_cf) {
