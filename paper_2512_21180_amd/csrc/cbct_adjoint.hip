@@ -1046,7 +1046,8 @@ constexpr long kMcBricks = 1024;
 int adjoint_mc_channels(const cbct_geom *g, int left)
 {
     const AdjPlan &p = g->adj;
-    if (!p.ok || p.NTmax > kMaxTapsMc)
+    // adjoint_mc gathers all angles in one range
+    if (!p.ok || p.split > 1 || p.NTmax > kMaxTapsMc)
         return 1;
     const BrickArgs A = brick_args(g->dev, p);
     if ((long)A.nbx * A.nby * A.nbz < kMcBricks)
