@@ -51,8 +51,10 @@
 // and two barriers for four angles.  When every wave found every
 // angle's ranges and each angle was tested, staged and gathered by itself the
 // clinical adjoint took 13.98 ms (now 12.70), the 64^3 one 220 us (150), four
-// channels of 128^3 x 180 x 256^2 6.0 ms (4.7).  Bound by VALU issue in the taps
-// where windows are tall, by the per-column set-up where runs are short.
+// channels of 128^3 x 180 x 256^2 6.0 ms (4.7).  Bound by the taps where windows
+// are tall (clinical case: LDS pipe busy 62 % of the cycles, a third of all with
+// second passes; the 6.5e9 VALU instructions take half of them at two cycles
+// each), by the per-column set-up where runs are short.
 // SOLO kernels do take every angle by itself (see take_solo); the bits are the same.
 
 #include <hip/hip_runtime.h>
@@ -687,13 +689,13 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, BrickAt at, int
         // of the group (all waves use them), from the records in that angle's
         // window, or, where fewer than four windows fit, from a copy in the
         // window's place before it is staged
-        for (int i0 = 0; i0 < n; i0 += kGroup) {
-            const int m = min(kGroup, n - i0);
+        for (int first = 0; first < n; first += kGroup) {
+            const int m = min(kGroup, n - first);
             const bool all = A.gw == kGroup;
-            if (i0 > 0)
+            if (first > 0)
                 __syncthreads();   // the previous group's readers are done
             if (w < m) {
-                const AngleEnt e = uniform_ent(list[i0 + w]);
+                const AngleEnt e = uniform_ent(list[first + w]);
                 float4 *cr = (float4 *)(lds + w * (all ? win : recs));
                 stage_columns(g, e, lane, cr);
                 if (!all) {
@@ -704,12 +706,12 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, BrickAt at, int
             }
             if (all) {
                 for (int i = 0; i < m; ++i)
-                    stage_window(uniform_ent(list[i0 + i]), lds + i * win + recs);
+                    stage_window(uniform_ent(list[first + i]), lds + i * win + recs);
                 if (w < m) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     ranges[w * 64 + lane] =
-                        column_ranges(g, uniform_ent(list[i0 + w]), pl, sg, inv_du,
+                        column_ranges(g, uniform_ent(list[first + w]), pl, sg, inv_du,
                                       (const float4 *)(lds + w * win));
                 }
             }
@@ -718,7 +720,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, BrickAt at, int
                 if (!all) {
                     __syncthreads();   // the windows' readers, or the ranges', are done
                     for (int j = 0; j < mi; ++j) {
-                        const AngleEnt e = uniform_ent(list[i0 + i + j]);
+                        const AngleEnt e = uniform_ent(list[first + i + j]);
                         float *yt = lds + j * win + recs;
                         stage_window(e, yt);
                         if (w == j)
@@ -727,7 +729,7 @@ __device__ __forceinline__ void gather_brick(const BrickArgs &A, BrickAt at, int
                 }
                 __syncthreads();
                 for (int j = 0; j < mi; ++j)
-                    gather(uniform_ent(list[i0 + i + j]), [&] { return ranges[(i + j) * 64 + lane]; },
+                    gather(uniform_ent(list[first + i + j]), [&] { return ranges[(i + j) * 64 + lane]; },
                            lds + j * win + recs);
             }
         }

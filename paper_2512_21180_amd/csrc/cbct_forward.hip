@@ -283,9 +283,11 @@ struct SweepArgs {
 };
 
 // Seven waves per SIMD (72 registers; the LDS of seven workgroups fits a CU).
-// The sweep is bound by VALU issue (5.2e9 wave instructions, the whole
-// of its 7.7 ms), so more waves only fill the gaps between dependent reads:
-// clinical forward 8.06 ms at five, 7.84 at six, 7.71 at seven.
+// The sweep is bound by the LDS pipe: its reads of two words and its 16-byte
+// stores keep it busy for all of the 1.65e7 cycles (clinical case), the 5.2e9
+// VALU instructions (two cycles for an add or FMA, four for a fraction, a
+// conversion or a 24-bit multiply-add) for three quarters; more waves fill the
+// gaps between dependent reads: 8.06 ms at five, 7.84 at six, 7.71 at seven.
 template <class SS, int R>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(7, 7)))
 forward_sweep(SweepArgs A, const float *__restrict__ vol, const float *__restrict__ volt,

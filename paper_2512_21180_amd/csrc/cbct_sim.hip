@@ -1,8 +1,9 @@
 // Projection-data simulator kernels (see cbct_sim.h): Philox4x32-10 counter
 // based random numbers, Poisson counts of the attenuated beam and the
 // negative-log normalisation (monochromatic, or polychromatic over energy
-// bins with the water-bone decomposition), or additive Gaussian noise.  One thread per
-// element; the Poisson rejection loop is bounded (64 trials).
+// bins with the water-bone decomposition), or additive Gaussian noise.  One
+// thread per element, but for the Poisson counts, which a wave decides together
+// (WavePoisson); the Poisson rejection loop is bounded (64 trials).
 #include <hip/hip_runtime.h>
 
 #include "cbct_internal.h"
@@ -247,7 +248,8 @@ struct WavePoisson {
                     trial = kExact;
                 } else {
                     // FP32 values of the first trial: |U|, us and V err by at
-                    // most 2^-23 of themselves plus 2^-32, the slope by a few
+                    // most 2^-23 of themselves plus 2^-27 (unif53 leaves out the
+                    // first word's last five bits), the slope by a few
                     // 2^-23 of itself
                     const float sl = __builtin_amdgcn_sqrtf((float)lam);
                     const float b = fmaf(2.53f, sl, 0.931f);

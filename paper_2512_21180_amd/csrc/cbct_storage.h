@@ -1,7 +1,6 @@
 // Storage conversions for the projector kernels: FP32 arithmetic on FP32,
 // BF16 or FP16 buffers (widened on load, rounded to nearest-even on store).
-// `raw` loads the stored bits into a 32-bit register (`buf_at`, FP32 only:
-// through a buffer resource, zero outside its range) and `wide` widens them:
+// `raw` loads the stored bits into a 32-bit register and `wide` widens them:
 // a kernel that keeps loads in flight across other work holds raw values and
 // widens them where they are used (widening, or packing two 16-bit values
 // into one register, right after the load would wait for it).
@@ -18,10 +17,6 @@ struct F32 {
     __device__ static float ld(const T *p, size_t i) { return p[i]; }
     using Raw = float;
     __device__ static Raw raw(const T *p, size_t i) { return p[i]; }
-    __device__ static Raw buf_at(__amdgpu_buffer_rsrc_t r, uint32_t byte_off)
-    {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, 0));
-    }
     __device__ static float wide(Raw x) { return x; }
     __device__ static void st(T *p, size_t i, float v) { p[i] = v; }
 };
