@@ -1,6 +1,6 @@
 // Peak probes of the projector's two on-chip limits on gfx950: vector FP32
-// FMA issue and LDS read bandwidth.  The projector kernels are bound by VALU
-// issue and on-chip gathers, not by HBM (Sec. 2.2's operators move each
+// FMA issue and LDS read bandwidth.  The projector kernels are bound by the VALU
+// and on-chip gathers, not by HBM (Sec. 2.2's operators move each
 // volume and sinogram element once from HBM); these kernels measure what the
 // chip delivers for those two, for comparison with the projector's counts.
 #include <hip/hip_runtime.h>
