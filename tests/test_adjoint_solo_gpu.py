@@ -54,3 +54,16 @@ def test_angles_one_by_one(dev, oracle, name):
     a, b = cbct.batch_adjoint([geo, other], [yg, z])
     assert torch.equal(a, one)
     assert torch.equal(b, cbct.adjoint(other, z))
+
+
+@pytest.mark.parametrize("channels", [2, 3, 4])
+def test_channels_of_two_angles(dev, channels):
+    """Channels gathered together take their angles as a group, a single call one by one."""
+    torch, cbct = dev
+    print(f"[adjoint solo] {channels} channels", flush=True)
+    geo = cbct.Geometry(GEOS["two angles, 16 layers"][0])
+    y = torch.tensor(np.random.default_rng(channels).standard_normal((channels,) + geo.sino_shape),
+                     dtype=torch.float32, device="cuda")
+    ref = torch.stack([cbct.adjoint(geo, y[c].contiguous()) for c in range(channels)])
+    assert ref.abs().max() > 0
+    assert torch.equal(cbct.adjoint(geo, y), ref)
